@@ -20,7 +20,10 @@
  * [sym_base + r*rank_stride, sym_base + (r+1)*rank_stride) of a single
  * symmetric allocation, and is served by its own workgroups.  Rank r's data
  * reaches another rank only through flagged packets written into that rank's
- * slice; no rank reads another rank's input.
+ * slice; no rank reads another rank's input.  At the sizes that are bound by
+ * bandwidth the gather half of a collective leaves the packets out: the rank
+ * that holds a block stores it into every rank's output, and then a
+ * completion flag into that rank's slice, which the rank waits for.
  *
  * Slice layout (a pure function of rank_stride and nranks, identical for
  * every call on a region, so a byte's role never changes between calls):

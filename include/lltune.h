@@ -80,6 +80,16 @@ int ll_buffered_plan(size_t count, ll_dtype dt, int nranks, size_t scratch_strid
  * elements in the iteration, two-shot chunk length in elements}.  Host only. */
 int ll_iteration_span(size_t count, size_t iter_count, uint32_t it, int nranks, ll_dtype dt, int64_t *out3);
 
+/* Geometry of a call on the ring kernels (the bandwidth-bound sizes): `tiles`
+ * tiles per chunk in a packet area of `area_bytes`, workgroups of `per_wg`
+ * waves, at most `max_wg` of them per rank.  mode: 0 AllReduce, 1
+ * ReduceScatter, 2 AllGather, 3 Broadcast, 4 Reduce.  out4 = {tiles, waves
+ * per rank, bytes of a packet slot, offset of the completion flags in the
+ * area}; LL_ERR_UNSUPPORTED if the area cannot hold the call (it then runs on
+ * another kernel).  Host only. */
+int ll_ring_shape(int nranks, int mode, uint64_t tiles, uint64_t area_bytes, uint64_t per_wg, uint64_t max_wg,
+                  uint64_t *out4);
+
 #ifdef __cplusplus
 }
 #endif

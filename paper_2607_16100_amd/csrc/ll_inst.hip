@@ -87,8 +87,19 @@ void fill_rtile(Table *t) {
   t->rtile[1][1][1][P] = k_rooted_tile<ProtoSent, 1, P, 1>;
 }
 
+template <class Pr, int DT, int P>
+void fill_ring(Table *t) {
+  constexpr int pr = std::is_same<Pr, ProtoLine>::value ? 1 : 0;
+  t->ring[RING_AR][pr][DT][P] = k_ring<Pr, DT, P, RING_AR>;
+  t->ring[RING_RS][pr][DT][P] = k_ring<Pr, DT, P, RING_RS>;
+}
+
 template <int P>
 void fill(Table *t) {
+  fill_ring<ProtoLL, 0, P>(t);
+  fill_ring<ProtoLL, 1, P>(t);
+  fill_ring<ProtoLine, 0, P>(t);
+  fill_ring<ProtoLine, 1, P>(t);
   fill_row<ProtoLL, 0, P>(t->k[PR_LL][0][P]);
   fill_row<ProtoLL, 1, P>(t->k[PR_LL][1][P]);
   fill_row<ProtoLine, 0, P>(t->k[PR_LINE][0][P]);

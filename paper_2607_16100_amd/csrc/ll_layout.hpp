@@ -140,6 +140,41 @@ inline uint64_t capacity(uint64_t stride, int P) {
   return lo * kAlign;
 }
 
+// Geometry of a ring call (ll_ring.hpp) in a packet area of area_bytes: `slot`
+// bytes of packets per peer, P-1 slots, then P-1 completion slots of one
+// 64-byte block per wave, whose last dword is the flag (where both flagged
+// formats keep one).  A wave owns kRingEntries positions of 1 KiB in every
+// slot; a Broadcast has a position per tile, an AllGather none.  The waves of
+// a rank, G, are as many as max_wg workgroups and the area hold, and no more
+// than the tiles need when every wave takes the same number of steps.
+constexpr uint64_t kRingEntries = 4;
+constexpr uint64_t kRingPacketBytes = 1024, kRingFlagBytes = 64;
+// 32-bit stream offsets with the top bit free for "nowhere" (ll_ring.hpp)
+constexpr uint64_t kRingMaxBytes = (2ull << 30) - (1ull << 20);
+enum RingMode { RING_AR = 0, RING_RS = 1, RING_AG = 2, RING_BCAST = 3, RING_REDUCE = 4 };
+
+struct RingShape {
+  uint64_t tiles, waves;  // tiles per chunk, waves per rank
+  uint64_t slot, flags;   // bytes of a slot, offset of the completion slots
+};
+
+inline bool ring_shape(int P, int mode, uint64_t tiles, uint64_t area_bytes, uint64_t per_wg, uint64_t max_wg,
+                       RingShape *out) {
+  const uint64_t avail = area_bytes / (uint64_t)(P - 1);  // per peer
+  const uint64_t fixed = mode == RING_BCAST ? tiles * kRingPacketBytes : 0;
+  const uint64_t per_wave =
+      kRingFlagBytes + (mode == RING_AG || mode == RING_BCAST ? 0 : kRingEntries * kRingPacketBytes);
+  if (tiles == 0 || avail < fixed) return false;
+  const uint64_t wg = std::min(max_wg, (avail - fixed) / (per_wave * per_wg));
+  if (wg == 0) return false;
+  const uint64_t steps = ceil_div(tiles, wg * per_wg);
+  out->tiles = tiles;
+  out->waves = ceil_div(ceil_div(tiles, steps), per_wg) * per_wg;
+  out->slot = mode == RING_AG ? 0 : (mode == RING_BCAST ? fixed : out->waves * kRingEntries * kRingPacketBytes);
+  out->flags = out->slot * (uint64_t)(P - 1);
+  return out->slot * (uint64_t)(P - 1) <= 0xFFFFFFFFull;
+}
+
 // Bounded scratch (multi-iteration calls with an input outside the region).
 // A scratch slice holds, per packet format, two sub-buffers, each sized like
 // that format's area for an input of D bytes; a call of M bytes per rank runs

@@ -8,6 +8,7 @@
 #pragma once
 
 #include "ll_kernels.hpp"
+#include "ll_ring.hpp"
 
 namespace llc {
 
@@ -44,6 +45,8 @@ struct Table {
   kernel_fn ttile[3][2][3][2][kMaxRanks + 1];
   // Broadcast / Reduce, one tile per workgroup: [8-byte packets, sentinel][Broadcast, Reduce][dtype][P]
   kernel_fn rtile[2][2][2][kMaxRanks + 1];
+  // ring kernels: [RingMode][8-byte packets, lines][dtype][P]
+  ring_fn ring[5][2][2][kMaxRanks + 1];
 };
 
 // Defined in the unit built for that rank count.

@@ -198,7 +198,7 @@ int status_of(void *stream, uint32_t **out) {
 std::map<std::tuple<int, const void *, int>, int> g_per_cu;  // guarded by g_mu
 
 // Largest grid of `fn` that is resident at once with `threads` per workgroup.
-int resident_grid(kernel_fn fn, int threads, int *grid_out) {
+int resident_grid(const void *fn, int threads, int *grid_out) {
   DevInfo d;
   int st = device_info(&d);
   if (st != LL_OK) return st;
@@ -208,12 +208,12 @@ int resident_grid(kernel_fn fn, int threads, int *grid_out) {
     t_last_hip = (int)e;
     return LL_ERR_HIP;
   }
-  const auto key = std::make_tuple(dev, reinterpret_cast<const void *>(fn), threads);
+  const auto key = std::make_tuple(dev, fn, threads);
   std::lock_guard<std::mutex> lk(g_mu);
   auto it = g_per_cu.find(key);
   if (it == g_per_cu.end()) {
     int per_cu = 0;
-    e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, reinterpret_cast<const void *>(fn), threads, 0);
+    e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, fn, threads, 0);
     if (e != hipSuccess) {
       t_last_hip = (int)e;
       return LL_ERR_HIP;
@@ -222,6 +222,10 @@ int resident_grid(kernel_fn fn, int threads, int *grid_out) {
   }
   *grid_out = it->second * d.cus;
   return LL_OK;
+}
+
+int resident_grid(kernel_fn fn, int threads, int *grid_out) {
+  return resident_grid(reinterpret_cast<const void *>(fn), threads, grid_out);
 }
 
 inline int esize_of(ll_dtype dt) { return dt == LL_BF16 ? 2 : 4; }
@@ -254,6 +258,7 @@ struct Plan {
   int64_t units;  // packet units per stream
   CallOpts o;     // the call's options
   bool rooted_tile = false;  // Broadcast / Reduce on the one-tile kernel
+  uint64_t area_bytes = 0;   // bytes of the call's packet area from a.area on
 };
 
 // Launch shape of the two-shot AllReduce with one wave per peer, measured on
@@ -395,7 +400,115 @@ uint32_t clear_slots(const Plan &pl) {
 
 int launch_kernel(kernel_fn fn, const Plan &pl, int W, int threads, void *stream);
 
+// ---------------------------------------------------------------- ring kernels
+// Total bytes (all ranks' inputs) from which a
+// call runs on a ring kernel (ll_ring.hpp), measured on MI355X at every rank
+// count against the kernel that served the call before, bfloat16, p50 of
+// back-to-back calls:
+//  - AllReduce, lines: 7 MiB over the ranks.  8 ranks: 768 KiB per rank 8.50
+//    us against 8.28 us, 1 MiB 9.20 against 10.62, 4 MiB 21.9 against 30.9,
+//    64 MiB 308 against 500; 4 ranks: 1 MiB 7.27 against 6.34, 2 MiB 8.95
+//    against 9.67; 2 ranks: 3 MiB 7.08 against 6.44, 4 MiB 7.32 against 7.52.
+//  - AllReduce, 8-byte packets: 5 MiB (8 ranks: 512 KiB per rank 8.77 against
+//    8.48, 1 MiB 13.8 against 15.2; 4 ranks: 1 MiB 7.82 against 8.28).
+//  - ReduceScatter: 32 MiB (8 ranks: 2 MiB per rank 12.6 against 9.7, 4 MiB
+//    17.5 against 17.8, 8 MiB 33.2 against 36.3; 4 ranks: 4 MiB 10.3 against
+//    9.3, 8 MiB 16.8 against 19.1).
+bool ring_size_ok(int mode, const Plan &pl, uint64_t total) {
+  const uint64_t MiB = 1024 * 1024;
+  const int P = pl.P;
+  switch (mode) {
+    case RING_AR: return pl.a.iters <= 1 && total * P >= (pl.proto == PR_LINE ? 7 : 5) * MiB;
+    case RING_RS: return total * P >= 32 * MiB;
+    default: return false;
+  }
+}
+
+// Waves per CU of a ring launch.  The kernels are bound by the fabric (about
+// 6.6 TB/s of reads and writes together), not by latency, from 4 waves per CU
+// on: 64 MiB at 8 ranks 312 us with 4, 308 with 8, 311 with 16; 16 MiB 84, 79
+// and 79-100.  Fewer waves also keep the ring small: 8 per CU are 56 MiB of
+// slots at 8 ranks, which stay in the memory-side cache.
+constexpr uint64_t kRingWavesPerCu = 8;
+
+// Whether a ring kernel serves this call: no tuning field set, every stream
+// 4-byte aligned, at most kRingMaxBytes per rank (32-bit stream offsets) and a size
+// for which it is the faster one.  Otherwise the call's other kernel runs.
+bool ring_serves(const Plan &pl, int *mode_out, uint64_t *total_out, uint64_t *chunk_out) {
+  int mode;
+  switch (pl.kind) {
+    case K_TWOSHOT: case K_TWOSHOT_WAVES: mode = RING_AR; break;
+    case K_RS: case K_RS_WAVES: mode = RING_RS; break;
+    default: return false;
+  }
+  const CallOpts &o = pl.o;
+  if (pl.proto == PR_SENT || o.forced_shape() || o.wave_units != 0 || o.wave_kernels != 0 || o.clear_slots != 0 ||
+      o.lag != 1 || o.first_wait != 0 || o.poll_gap != 0 || o.phases != nullptr)
+    return false;
+  if (pl.a.al4 == 0 || (pl.a.in != nullptr && pl.a.in_al4 == 0)) return false;
+  const int es = pl.dt == LL_BF16 ? 2 : 4;
+  const bool blocks = mode == RING_RS || mode == RING_AG;  // P chunks of n elements
+  const uint64_t total = (uint64_t)pl.a.n * (uint64_t)es * (blocks ? (uint64_t)pl.P : 1);
+  if (total > L::kRingMaxBytes || !ring_size_ok(mode, pl, total)) return false;
+  *mode_out = mode;
+  *total_out = total;
+  *chunk_out = blocks ? total / (uint64_t)pl.P : L::twoshot_chunk((uint64_t)pl.a.n, pl.P, es) * (uint64_t)es;
+  return true;
+}
+
+// Launches the call on a ring kernel if one serves it: true, with the
+// call's status in *rc; false if the call must run another way.
+bool ring_launch(const Plan &pl, void *stream, int *rc) {
+  int mode;
+  uint64_t total, chunk;
+  if (!ring_serves(pl, &mode, &total, &chunk)) return false;
+  const int P = pl.P;
+  const ring_fn fn = table().ring[mode][pl.proto == PR_LINE ? 1 : 0][pl.dt][P];
+  int cap = 0;
+  DevInfo d;
+  if ((*rc = resident_grid(reinterpret_cast<const void *>(fn), kRingThreads, &cap)) != LL_OK) return true;
+  if ((*rc = device_info(&d)) != LL_OK) return true;
+  constexpr uint64_t per_wg = kRingThreads / 64;
+  const uint64_t max_wg = std::min((uint64_t)cap, kRingWavesPerCu * (uint64_t)d.cus / per_wg) / (uint64_t)P;
+  const uint64_t tile = pl.proto == PR_LINE ? RingTile<ProtoLine>::kPayload : RingTile<ProtoLL>::kPayload;
+  L::RingShape sh;
+  if (!L::ring_shape(P, mode, L::ceil_div(chunk, tile), pl.area_bytes, per_wg, max_wg, &sh)) return false;
+  RingArgs a;
+  memset(&a, 0, sizeof a);
+  a.sym = pl.a.sym;
+  a.stride = pl.a.stride;
+  a.in = pl.a.in != nullptr ? pl.a.in : pl.a.sym;  // by default inside the region, at offset 0 of every slice
+  a.in_stride = pl.a.in != nullptr ? pl.a.in_stride : pl.a.stride;
+  a.out = pl.a.out;
+  a.out_pitch = mode == RING_RS || mode == RING_REDUCE ? 0 : total;
+  a.area = pl.a.area;
+  a.flags = pl.a.area + sh.flags;
+  a.timeout = pl.o.timeout;
+  a.stamps = pl.o.stamps;
+  a.total = (uint32_t)total;
+  a.chunk = (uint32_t)chunk;
+  a.slot = (uint32_t)sh.slot;
+  a.tiles = (uint32_t)sh.tiles;
+  a.waves = (uint32_t)sh.waves;
+  a.epoch = pl.a.epoch;
+  a.mute = pl.o.mute;
+  a.root = (uint32_t)pl.a.root;
+  a.grid = (uint32_t)(sh.waves / per_wg * (uint64_t)P);
+  if ((*rc = status_of(stream, &a.status)) != LL_OK) return true;
+  hipLaunchKernelGGL(fn, dim3(a.grid), dim3(kRingThreads), 0, (hipStream_t)stream, a);
+  const hipError_t e = hipGetLastError();
+  if (pl.o.grid_out) *pl.o.grid_out = (int)a.grid;
+  if (pl.o.threads_out) *pl.o.threads_out = kRingThreads;
+  if (e != hipSuccess) {
+    t_last_hip = (int)e;
+    *rc = LL_ERR_HIP;
+  }
+  return true;
+}
+
 int launch(const Plan &pl, void *stream) {
+  int ring_rc = LL_OK;
+  if (ring_launch(pl, stream, &ring_rc)) return ring_rc;
   const bool two_waves = pl.kind == K_TWOSHOT_WAVES || pl.kind == K_RS_WAVES || pl.kind == K_AG_WAVES;
   const bool wave_kernel = pl.kind == K_ONESHOT_WAVES || two_waves;
   const int wpr = pl.proto == PR_SENT ? 1 : (pl.proto == PR_LINE ? 2 : 0);
@@ -518,6 +631,7 @@ struct Region {
   uint64_t area_of(int proto) const {
     return proto == PR_LINE ? cap + a8 : (proto == PR_SENT ? cap + a8 + a128 + aa : cap);
   }
+  uint64_t area_bytes(int proto) const { return proto == PR_LINE ? a128 : (proto == PR_SENT ? as : a8); }
   uint64_t atomic_area() const { return cap + a8 + a128; }
 };
 
@@ -926,6 +1040,7 @@ int ll_allreduce_ex(void *sym_base, size_t rank_stride, void *out, size_t count,
     return launch(pl, stream);
   }
   plan_allreduce(&pl, algo, count, es, nranks, count, [&](int proto) { return rg.area_of(proto); });
+  pl.area_bytes = rg.area_bytes(pl.proto);
   return launch(pl, stream);
 }
 
@@ -1027,6 +1142,20 @@ int ll_iteration_span(size_t count, size_t iter_count, uint32_t it, int nranks, 
   return LL_OK;
 }
 
+int ll_ring_shape(int nranks, int mode, uint64_t tiles, uint64_t area_bytes, uint64_t per_wg, uint64_t max_wg,
+                  uint64_t *out4) {
+  if (out4 == nullptr || nranks < 2 || nranks > LL_MAX_RANKS || mode < L::RING_AR || mode > L::RING_REDUCE ||
+      per_wg == 0)
+    return LL_ERR_INVALID;
+  L::RingShape sh;
+  if (!L::ring_shape(nranks, mode, tiles, area_bytes, per_wg, max_wg, &sh)) return LL_ERR_UNSUPPORTED;
+  out4[0] = sh.tiles;
+  out4[1] = sh.waves;
+  out4[2] = sh.slot;
+  out4[3] = sh.flags;
+  return LL_OK;
+}
+
 // A bounded-scratch AllReduce through the scratch region at scratch_base,
 // laid out for `layout_P` ranks (nranks <= layout_P: a call uses the first
 // nranks slices and the first nranks-1 slots of every area, whose offsets
@@ -1100,6 +1229,7 @@ static int buffered_call(const void *in, void *out, size_t count, ll_dtype dt, l
     return proto == PR_LINE ? 2 * a8 : (proto == PR_SENT ? 2 * (a8 + a128) : (uint64_t)0);
   });
   pl.a.sub_bytes = pl.proto == PR_LINE ? a128 : (pl.proto == PR_SENT ? as : a8);
+  pl.area_bytes = 2 * pl.a.sub_bytes;
   st = launch(pl, stream);
   if (st == LL_OK && epochs_used != nullptr) *epochs_used = (uint32_t)iters;
   return st;
@@ -1237,6 +1367,7 @@ int ll_reduce_scatter_ex(void *sym_base, size_t rank_stride, void *out, size_t r
   pl.a.n = (int64_t)recvcount;
   pl.a.al4 = (chunk_bytes % 4 == 0) ? 1u : 0u;
   pl.a.area = rg.area_of(pl.proto);
+  pl.area_bytes = rg.area_bytes(pl.proto);
   pl.a.slot = slot_bytes(pl.proto, chunk_bytes);
   pl.units = units_of(pl.proto, chunk_bytes);
   return launch(pl, stream);
@@ -1281,6 +1412,7 @@ int ll_allgather_ex(void *sym_base, size_t rank_stride, void *out, size_t sendco
   pl.a.n = (int64_t)sendcount;
   pl.a.al4 = (in_bytes % 4 == 0) ? 1u : 0u;
   pl.a.area = rg.area_of(pl.proto);
+  pl.area_bytes = rg.area_bytes(pl.proto);
   pl.a.slot = slot_bytes(pl.proto, in_bytes);
   pl.units = units_of(pl.proto, in_bytes);
   return launch(pl, stream);
@@ -1326,6 +1458,7 @@ static int rooted_call(Kind kind, void *sym_base, size_t rank_stride, void *out,
   pl.a.al4 = (in_bytes % 4 == 0) ? 1u : 0u;
   pl.a.root = root;
   pl.a.area = rg.area_of(pl.proto);
+  pl.area_bytes = rg.area_bytes(pl.proto);
   pl.a.slot = slot_bytes(pl.proto, in_bytes);
   pl.units = units_of(pl.proto, in_bytes);
   return launch(pl, stream);

@@ -1,0 +1,203 @@
+"""GPU parity of the ring kernels (the bandwidth-bound sizes) against the CPU
+oracle: the edges of their sizes, tiles and chunks, every collective and
+flagged format, calls mixed with other kernels on one region, graph replays
+and muted ranks."""
+from __future__ import annotations
+
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+import oracle  # noqa: E402
+from paper_2607_16100_amd import workloads as wl  # noqa: E402
+
+if torch.cuda.is_available():
+    from paper_2607_16100_amd import llcoll as ll  # noqa: E402
+    from paper_2607_16100_amd.region import SymRegion  # noqa: E402
+else:  # pragma: no cover
+    pytest.skip("no GPU", allow_module_level=True)
+
+NP = {"f32": np.uint32, "bf16": np.uint16}
+ES = {"f32": 4, "bf16": 2}
+KIB, MIB = 1 << 10, 1 << 20
+RING_THREADS = 128
+
+
+def stream():
+    return torch.cuda.current_stream().cuda_stream
+
+
+def opts(**kw):
+    kw.setdefault("poll_timeout", 20_000_000)
+    return ll.Options(report=True, **kw)
+
+
+def call(reg, op, n, p, root, opt, **kw):
+    f = {"allreduce": lambda: reg.allreduce(n, opt=opt, **kw), "reduce_scatter": lambda: reg.reduce_scatter(n // p, opt=opt, **kw),
+         "allgather": lambda: reg.allgather(n, opt=opt, **kw), "broadcast": lambda: reg.broadcast(n, root, opt=opt, **kw),
+         "reduce": lambda: reg.reduce(n, root, opt=opt, **kw)}[op]
+    return f()
+
+
+def want_of(op, x, root):
+    return {"allreduce": lambda: oracle.allreduce(x), "reduce_scatter": lambda: oracle.reduce_scatter(x),
+            "allgather": lambda: oracle.allgather(x), "broadcast": lambda: oracle.broadcast(x, root),
+            "reduce": lambda: oracle.reduce(x, root)}[op]().reshape(-1)
+
+
+def out_elems(op, p, n):
+    return {"reduce_scatter": n, "allgather": p * p * n, "reduce": n}.get(op, p * n)
+
+
+def check(reg, op, n, p, dtype, root, ring, what, opt=None, **kw):
+    print(what, flush=True)
+    x = wl.uniform(p, n, dtype, seed=n % 1009 + p)
+    reg.write_inputs(x)
+    reg.out.fill_(0xA5)
+    opt = opt or opts()
+    assert call(reg, op, n, p, root, opt, **kw) == ll.LL_OK, what
+    assert ll.ll_check(stream()) == ll.LL_OK, what
+    if p != 2:  # at 2 ranks the wave-per-peer kernels have workgroups of the same size
+        assert (opt.threads == RING_THREADS) == ring, f"{what}: on a workgroup of {opt.threads} threads"
+    total = out_elems(op, p, n)
+    got = reg.read_out(total, NP[dtype])
+    bad = np.flatnonzero(got != want_of(op, x, root))
+    assert bad.size == 0, f"{what}: {bad.size} elements differ, first at {bad[0]}"
+    if total * ES[dtype] < reg.out.numel():
+        assert (reg.out[total * ES[dtype]:total * ES[dtype] + 4096] == 0xA5).all(), f"{what}: wrote past the outputs"
+
+
+# (operation, first size per rank in bytes on the ring, by rank count)
+FIRST = {
+    "allreduce": lambda p: -(-7 * MIB // p), "reduce_scatter": lambda p: -(-32 * MIB // p),
+}
+
+
+@pytest.mark.parametrize("op", list(FIRST))
+@pytest.mark.parametrize("p,dtype", [(2, "bf16"), (3, "f32"), (4, "bf16"), (5, "f32"), (7, "bf16"), (8, "f32")])
+def test_sizes_at_the_edges(op, p, dtype):
+    """Just below and at the first ring size, and above it: whole tiles, a
+    word more and less, ragged chunks, a last chunk of one word."""
+    es = ES[dtype]
+    unit = p if op == "reduce_scatter" else 1  # ReduceScatter inputs are P equal chunks
+    even = 2 if dtype == "bf16" else 1          # whole words
+    first = -(-FIRST[op](p) // es)
+    first = -(-first // (unit * even)) * unit * even
+    tile = 960 // es * (1 if op == "allgather" else p)  # one more tile in every chunk
+    top = first + 40 * tile
+    tiles = -(-first // tile)
+    sizes = [first - unit * even, first, first + unit * even, tile * (tiles + 1) // (unit * even) * unit * even,
+             top - 3 * unit * even, top]
+    if op == "allreduce":  # chunks are rounded up to 16 bytes: the last one is short
+        c = -(-top // p) // (16 // es) * (16 // es)
+        sizes.append((p - 1) * c + even)
+    reg = SymRegion(p, top, dtype, out_elems=out_elems(op, p, top) + 4096)
+    reg.init()
+    for root in ((p - 1, 1) if op in ("broadcast", "reduce") else (0,)):
+        for i, n in enumerate(sizes):
+            ring = i > 0
+            check(reg, op, n, p, dtype, root, ring if n >= first else False, f"{op} P={p} {dtype} n={n} root={root}")
+
+
+@pytest.mark.parametrize("op", list(FIRST))
+@pytest.mark.parametrize("proto", ["packet8", "line128"])
+def test_named_formats_and_many_steps(op, proto):
+    """8-byte packets and lines, at a size where the ring goes round several
+    times, and a region that holds that format only."""
+    p, dtype = 8, "bf16"
+    n = {"allreduce": 10 * MIB + 6, "reduce_scatter": 8 * MIB, "allgather": MIB + 2}.get(op, 10 * MIB + 6)
+    algo = "twoshot_waves" if proto == "packet8" else "twoshot_line_waves"
+    reg = SymRegion(p, n, dtype, out_elems=out_elems(op, p, n) + 4096, sized_for=algo)
+    reg.init()
+    for k in range(2):
+        kw = {"algo": algo} if op == "allreduce" else {"proto": proto}
+        check(reg, op, n, p, dtype, 5, True, f"{op} {proto} call {k}", **kw)
+
+
+@pytest.mark.parametrize("p", [3, 8])
+def test_streams_that_start_on_half_a_word_run_elsewhere(p):
+    """An odd bfloat16 count puts every other output on half a word: those
+    calls keep their kernel."""
+    n = 8 * MIB // 2 + 1
+    reg = SymRegion(p, n, "bf16", out_elems=p * n + 4096)
+    reg.init()
+    check(reg, "allreduce", n, p, "bf16", 0, False, f"odd count P={p}")
+    check(reg, "allreduce", n - 1, p, "bf16", 0, True, f"even count P={p}")
+
+
+def test_ring_and_other_kernels_share_a_region():
+    """Calls of every kind and size in turn on one region, epochs one apart
+    and up to the last one: no call takes another's packets for its own."""
+    p, dtype = 8, "f32"
+    n = 4 * MIB // 4
+    reg = SymRegion(p, n, dtype, out_elems=p * p * n // 8 + 4096)
+    reg.init()
+    plan = [("allreduce", n, {}), ("allreduce", 4096, {}), ("allreduce", 16384, {"algo": "oneshot_line_waves"}),
+            ("allreduce", n, {}), ("broadcast", n - 1, {}), ("allreduce", 65536, {"algo": "twoshot_line"}),
+            ("reduce", n - 2, {}), ("allgather", n // 8, {}), ("allreduce", n, {"algo": "twoshot_waves"}),
+            ("reduce_scatter", n, {}), ("allreduce", 30001, {}), ("allgather", n // 8 - 1, {"proto": "packet8"}),
+            ("allreduce", n - 5, {})]
+    for start in (0, 0xFFFFFFFF - len(plan)):
+        reg.epoch = start
+        for op, m, kw in plan:
+            x = wl.normal(p, m, dtype, seed=m % 77 + reg.epoch % 5)
+            reg.write_inputs(x)
+            print(op, m, kw, reg.epoch, flush=True)
+            assert call(reg, op, m, p, 2, opts(), **kw) == ll.LL_OK
+            assert ll.ll_check(stream()) == ll.LL_OK
+            got = reg.read_out(out_elems(op, p, m), NP[dtype])
+            assert np.array_equal(got, want_of(op, x, 2)), f"{op} {m} {kw} epoch {reg.epoch}"
+    assert reg.epoch == 0xFFFFFFFF
+
+
+@pytest.mark.parametrize("op", list(FIRST))
+def test_muted_rank_times_out(op):
+    """A rank that publishes nothing is noticed by its peers, and the region
+    works again after ll_init."""
+    p, dtype, root = 8, "bf16", 1
+    n = {"reduce_scatter": 16 * MIB}.get(op, MIB)
+    reg = SymRegion(p, n, dtype, out_elems=out_elems(op, p, n))
+    reg.init()
+    mute = root if op == "broadcast" else 6
+    reg.write_inputs(wl.normal(p, n, dtype, seed=3))
+    print(op, "muted", flush=True)
+    assert call(reg, op, n, p, root, opts(poll_timeout=200_000, mute_rank=mute)) == ll.LL_OK
+    assert ll.ll_check(stream()) == ll.LL_ERR_TIMEOUT
+    # the first wait to expire is a peer's, for the muted rank, or the muted
+    # rank's own, for the outputs its peers cannot finish
+    rank, missing, _ = ll.ll_last_timeout()
+    assert missing == 1 << mute if rank != mute else missing
+    reg.init()
+    check(reg, op, n, p, dtype, root, True, f"{op} after the timeout")
+
+
+@pytest.mark.parametrize("op,n", [("allreduce", 2 * MIB)])
+def test_graph_replays(op, n):
+    """Captured ring calls replayed several times, the region reset and new
+    inputs written before each replay."""
+    p, dtype = 8, "bf16"
+    reg = SymRegion(p, n, dtype, out_elems=out_elems(op, p, n))
+    reg.init()
+    side = torch.cuda.Stream()
+    with torch.cuda.stream(side):
+        assert call(reg, op, n, p, 3, None) == ll.LL_OK
+    torch.cuda.synchronize()
+    reg.init(side)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=side):
+        for i in range(3):
+            assert call(reg, op, n, p, 3, None, epoch=1 + i) == ll.LL_OK
+    for rep in range(3):
+        x = wl.normal(p, n, dtype, sigma=10.0 ** (rep - 1), seed=40 + rep)
+        print(op, "replay", rep, flush=True)
+        reg.write_inputs(x)
+        reg.init()
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert ll.ll_check(side.cuda_stream) == ll.LL_OK
+        assert np.array_equal(reg.read_out(out_elems(op, p, n), NP[dtype]), want_of(op, x, 3)), f"{op} replay {rep}"
