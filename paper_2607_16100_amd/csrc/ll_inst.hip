@@ -92,6 +92,7 @@ void fill_ring(Table *t) {
   constexpr int pr = std::is_same<Pr, ProtoLine>::value ? 1 : 0;
   t->ring[RING_AR][pr][DT][P] = k_ring<Pr, DT, P, RING_AR>;
   t->ring[RING_RS][pr][DT][P] = k_ring<Pr, DT, P, RING_RS>;
+  t->ring[RING_AG][pr][DT][P] = k_ring<Pr, DT, P, RING_AG>;
 }
 
 template <int P>

@@ -401,7 +401,7 @@ uint32_t clear_slots(const Plan &pl) {
 int launch_kernel(kernel_fn fn, const Plan &pl, int W, int threads, void *stream);
 
 // ---------------------------------------------------------------- ring kernels
-// Total bytes (all ranks' inputs) from which a
+// Total bytes (all ranks' inputs; AllGather: one rank's output) from which a
 // call runs on a ring kernel (ll_ring.hpp), measured on MI355X at every rank
 // count against the kernel that served the call before, bfloat16, p50 of
 // back-to-back calls:
@@ -414,12 +414,17 @@ int launch_kernel(kernel_fn fn, const Plan &pl, int W, int threads, void *stream
 //  - ReduceScatter: 32 MiB (8 ranks: 2 MiB per rank 12.6 against 9.7, 4 MiB
 //    17.5 against 17.8, 8 MiB 33.2 against 36.3; 4 ranks: 4 MiB 10.3 against
 //    9.3, 8 MiB 16.8 against 19.1).
+//  - AllGather: 128 KiB of output per rank from 4 ranks up, 256 KiB below (8
+//    ranks: 64 KiB 3.03 against 2.91, 128 KiB 2.97 against 3.09, 2 MiB 6.26
+//    against 11.8, 16 MiB 26.4 against 67.4; 2 ranks: 128 KiB 2.73 against
+//    2.61, 256 KiB 2.70 against 2.94).
 bool ring_size_ok(int mode, const Plan &pl, uint64_t total) {
-  const uint64_t MiB = 1024 * 1024;
+  const uint64_t KiB = 1024, MiB = 1024 * 1024;
   const int P = pl.P;
   switch (mode) {
     case RING_AR: return pl.a.iters <= 1 && total * P >= (pl.proto == PR_LINE ? 7 : 5) * MiB;
     case RING_RS: return total * P >= 32 * MiB;
+    case RING_AG: return total >= (P >= 4 ? 128 : 256) * KiB;
     default: return false;
   }
 }
@@ -439,6 +444,7 @@ bool ring_serves(const Plan &pl, int *mode_out, uint64_t *total_out, uint64_t *c
   switch (pl.kind) {
     case K_TWOSHOT: case K_TWOSHOT_WAVES: mode = RING_AR; break;
     case K_RS: case K_RS_WAVES: mode = RING_RS; break;
+    case K_AG: case K_AG_WAVES: mode = RING_AG; break;
     default: return false;
   }
   const CallOpts &o = pl.o;
@@ -1397,7 +1403,11 @@ int ll_allgather_ex(void *sym_base, size_t rank_stride, void *out, size_t sendco
   st = region_of(rank_stride, nranks, in_bytes, &rg);
   if (st != LL_OK) return st;
   if (proto == LL_PROTO_AUTO) {
-    proto = proto_choice(auto_proto(in_bytes * nranks, nranks, o.sentinel_ok(), true), auto_formats(rg.fmt, o));
+    // from the size where the ring AllGather runs, its packets carry no data
+    // and no format is faster than lines (8 ranks, 128 KiB per rank sent: 4.7
+    // us, sentinel units 6.4)
+    const bool ring = in_bytes % 4 == 0 && in_bytes * nranks >= (nranks >= 4 ? 128u << 10 : 256u << 10);
+    proto = proto_choice(auto_proto(in_bytes * nranks, nranks, o.sentinel_ok() && !ring, true), auto_formats(rg.fmt, o));
     if (proto == LL_PROTO_AUTO) return LL_ERR_SCRATCH;
   }
   if ((rg.fmt & proto_fmt(proto)) == 0) return LL_ERR_SCRATCH;

@@ -73,6 +73,7 @@ def check(reg, op, n, p, dtype, root, ring, what, opt=None, **kw):
 # (operation, first size per rank in bytes on the ring, by rank count)
 FIRST = {
     "allreduce": lambda p: -(-7 * MIB // p), "reduce_scatter": lambda p: -(-32 * MIB // p),
+    "allgather": lambda p: -(-(128 if p >= 4 else 256) * KIB // p),
 }
 
 
@@ -174,7 +175,7 @@ def test_muted_rank_times_out(op):
     check(reg, op, n, p, dtype, root, True, f"{op} after the timeout")
 
 
-@pytest.mark.parametrize("op,n", [("allreduce", 2 * MIB)])
+@pytest.mark.parametrize("op,n", [("allreduce", 2 * MIB), ("allgather", 65536)])
 def test_graph_replays(op, n):
     """Captured ring calls replayed several times, the region reset and new
     inputs written before each replay."""
