@@ -93,6 +93,8 @@ void fill_ring(Table *t) {
   t->ring[RING_AR][pr][DT][P] = k_ring<Pr, DT, P, RING_AR>;
   t->ring[RING_RS][pr][DT][P] = k_ring<Pr, DT, P, RING_RS>;
   t->ring[RING_AG][pr][DT][P] = k_ring<Pr, DT, P, RING_AG>;
+  t->ring[RING_BCAST][pr][DT][P] = k_ring<Pr, DT, P, RING_BCAST>;
+  t->ring[RING_REDUCE][pr][DT][P] = k_ring<Pr, DT, P, RING_REDUCE>;
 }
 
 template <int P>

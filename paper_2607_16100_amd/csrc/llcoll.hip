@@ -418,6 +418,13 @@ int launch_kernel(kernel_fn fn, const Plan &pl, int W, int threads, void *stream
 //    ranks: 64 KiB 3.03 against 2.91, 128 KiB 2.97 against 3.09, 2 MiB 6.26
 //    against 11.8, 16 MiB 26.4 against 67.4; 2 ranks: 128 KiB 2.73 against
 //    2.61, 256 KiB 2.70 against 2.94).
+//  - Broadcast, Reduce (bytes per rank): at 8 ranks, a rank per XCD, 128 KiB
+//    (Broadcast 64 KiB 4.62 against 3.90, 128 KiB 4.89 against 5.08, 4 MiB
+//    12.4 against 39.6; Reduce 4.78 against 5.24 and 18.0 against 38.4).  At
+//    4-7 ranks Broadcast 1 MiB (4 ranks: 512 KiB 4.74 against 4.53, 1 MiB
+//    5.29 against 6.10), Reduce 2 MiB (5 ranks: 1 MiB 6.57 against 5.62,
+//    4 MiB 13.0 against 14.8).  At 2-3 ranks Broadcast 4 MiB (2 ranks: 1 MiB
+//    4.36 against 4.05, 4 MiB 6.54 against 7.01), Reduce 16 MiB.
 bool ring_size_ok(int mode, const Plan &pl, uint64_t total) {
   const uint64_t KiB = 1024, MiB = 1024 * 1024;
   const int P = pl.P;
@@ -425,7 +432,8 @@ bool ring_size_ok(int mode, const Plan &pl, uint64_t total) {
     case RING_AR: return pl.a.iters <= 1 && total * P >= (pl.proto == PR_LINE ? 7 : 5) * MiB;
     case RING_RS: return total * P >= 32 * MiB;
     case RING_AG: return total >= (P >= 4 ? 128 : 256) * KiB;
-    default: return false;
+    case RING_BCAST: return total >= (P == 8 ? 128 * KiB : (P >= 4 ? 1 * MiB : 4 * MiB));
+    default: return total >= (P == 8 ? 128 * KiB : (P >= 4 ? 2 * MiB : 16 * MiB));
   }
 }
 
@@ -445,6 +453,8 @@ bool ring_serves(const Plan &pl, int *mode_out, uint64_t *total_out, uint64_t *c
     case K_TWOSHOT: case K_TWOSHOT_WAVES: mode = RING_AR; break;
     case K_RS: case K_RS_WAVES: mode = RING_RS; break;
     case K_AG: case K_AG_WAVES: mode = RING_AG; break;
+    case K_BCAST: mode = RING_BCAST; break;
+    case K_REDUCE: mode = RING_REDUCE; break;
     default: return false;
   }
   const CallOpts &o = pl.o;

@@ -74,6 +74,8 @@ def check(reg, op, n, p, dtype, root, ring, what, opt=None, **kw):
 FIRST = {
     "allreduce": lambda p: -(-7 * MIB // p), "reduce_scatter": lambda p: -(-32 * MIB // p),
     "allgather": lambda p: -(-(128 if p >= 4 else 256) * KIB // p),
+    "broadcast": lambda p: 128 * KIB if p == 8 else (MIB if p >= 4 else 4 * MIB),
+    "reduce": lambda p: 128 * KIB if p == 8 else (2 * MIB if p >= 4 else 16 * MIB),
 }
 
 
@@ -175,7 +177,7 @@ def test_muted_rank_times_out(op):
     check(reg, op, n, p, dtype, root, True, f"{op} after the timeout")
 
 
-@pytest.mark.parametrize("op,n", [("allreduce", 2 * MIB), ("allgather", 65536)])
+@pytest.mark.parametrize("op,n", [("allreduce", 2 * MIB), ("allgather", 65536), ("broadcast", 65536 * 3), ("reduce", MIB)])
 def test_graph_replays(op, n):
     """Captured ring calls replayed several times, the region reset and new
     inputs written before each replay."""
