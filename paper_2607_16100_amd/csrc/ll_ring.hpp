@@ -16,14 +16,16 @@
 //    peer instead of a slot position per tile, so the packets of a call of any
 //    size live in at most 56 MiB at 8 ranks and never reach HBM.  Each peer's
 //    packets are the credit to go on (see kRingEntries), so a ring needs no
-//    counter, no barrier and no second buffer.
+//    counter, no barrier and no second buffer; a bounded-scratch call needs no
+//    iterations.
 //  - Waves that work alone.  A wave takes a tile of every chunk: it sends P-1
 //    tiles and reduces one, all in registers, with no LDS and no workgroup
 //    barrier, and its next tile's packets go out before it waits.
 // Measured (8 ranks, bfloat16 unless said, against the kernels that pass the
 // result through scratch): AllReduce 1 MiB 10.7 -> 9.2 us, 4 MiB 31.1 -> 22,
 // 16 MiB 124 -> 79, 64 MiB of binary32 500 -> 308; AllGather 448 KiB sent
-// 17.7 -> 8.1; Broadcast 16 MiB 146 -> 67; Reduce 16 MiB 146 -> 65.
+// 17.7 -> 8.1; Broadcast 16 MiB 146 -> 67; Reduce 16 MiB 146 -> 65; bounded
+// scratch, 32 MiB in 1 MiB iterations 345 -> 161.
 //
 // Grid = P * W workgroups of kRingThreads threads; workgroup b serves rank
 // r = b % P, and its waves are numbered g = (b / P) * waves + wave, G of them

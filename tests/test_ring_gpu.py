@@ -16,7 +16,7 @@ from paper_2607_16100_amd import workloads as wl  # noqa: E402
 
 if torch.cuda.is_available():
     from paper_2607_16100_amd import llcoll as ll  # noqa: E402
-    from paper_2607_16100_amd.region import SymRegion  # noqa: E402
+    from paper_2607_16100_amd.region import ScratchRegion, SymRegion  # noqa: E402
 else:  # pragma: no cover
     pytest.skip("no GPU", allow_module_level=True)
 
@@ -154,6 +154,28 @@ def test_ring_and_other_kernels_share_a_region():
             got = reg.read_out(out_elems(op, p, m), NP[dtype])
             assert np.array_equal(got, want_of(op, x, 2)), f"{op} {m} {kw} epoch {reg.epoch}"
     assert reg.epoch == 0xFFFFFFFF
+
+
+@pytest.mark.parametrize("in_place", [False, True])
+@pytest.mark.parametrize("p,dtype,iter_bytes", [(2, "f32", 4096), (5, "bf16", 8192), (7, "f32", 20000), (8, "bf16", 1 << 18)])
+def test_bounded_scratch_goes_round_the_ring(p, dtype, iter_bytes, in_place):
+    """Scratch regions that hold a few waves' rings: dozens to hundreds of
+    steps, two calls, from epoch 1."""
+    es = ES[dtype]
+    n = 120 * iter_bytes // es + 2
+    if iter_bytes > 65536:
+        n = 9 * iter_bytes // es + 14
+    reg = ScratchRegion(p, n, dtype, iter_bytes=iter_bytes, in_place=in_place)
+    reg.init()
+    for k, algo in enumerate(("auto", "twoshot_waves", "twoshot_line", "auto")):
+        x = wl.normal(p, n, dtype, seed=10 * k + p)
+        reg.write_inputs(x)
+        opt = opts()
+        print(f"P={p} {dtype} {iter_bytes} in_place={in_place} {algo}", flush=True)
+        assert reg.allreduce(n, algo, opt=opt) == ll.LL_OK
+        assert ll.ll_check(stream()) == ll.LL_OK
+        assert opt.threads == RING_THREADS and reg.last_iters > 1
+        assert np.array_equal(reg.read_out(p * n, NP[dtype]).reshape(p, n), oracle.allreduce(x)), algo
 
 
 @pytest.mark.parametrize("op", list(FIRST))
