@@ -200,20 +200,15 @@ std::map<std::tuple<int, const void *, int>, int> g_per_cu;  // guarded by g_mu
 // Largest grid of `fn` that is resident at once with `threads` per workgroup.
 int resident_grid(const void *fn, int threads, int *grid_out) {
   DevInfo d;
-  int st = device_info(&d);
-  if (st != LL_OK) return st;
   int dev = 0;
-  hipError_t e = hipGetDevice(&dev);
-  if (e != hipSuccess) {
-    t_last_hip = (int)e;
-    return LL_ERR_HIP;
-  }
+  const int st = device_info(&d, &dev);
+  if (st != LL_OK) return st;
   const auto key = std::make_tuple(dev, fn, threads);
   std::lock_guard<std::mutex> lk(g_mu);
   auto it = g_per_cu.find(key);
   if (it == g_per_cu.end()) {
     int per_cu = 0;
-    e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, fn, threads, 0);
+    const hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, fn, threads, 0);
     if (e != hipSuccess) {
       t_last_hip = (int)e;
       return LL_ERR_HIP;
@@ -663,19 +658,28 @@ int64_t units_of(int proto, uint64_t bytes) {
   return proto == PR_LINE ? ProtoLine::units(words) : (proto == PR_SENT ? ProtoSent::units(words) : ProtoLL::units(words));
 }
 
+// The layout is a pure function of (rank_stride, P) that takes a binary search
+// of some 20 steps; a thread keeps the last one it worked out, since a program
+// calls on one region many times in a row.
 int region_of(size_t rank_stride, int P, uint64_t in_bytes, Region *rg) {
-  const unsigned fmt = L::formats_of(rank_stride);
-  const uint64_t cap = L::capacity(rank_stride, P);
-  if (L::slice_for(cap, P, fmt) > rank_stride) return LL_ERR_SCRATCH;
+  struct Last {
+    size_t stride = 0;
+    int P = 0;
+    Region rg;
+  };
+  static thread_local Last last;
+  if (last.stride != rank_stride || last.P != P) {
+    const unsigned fmt = L::formats_of(rank_stride);
+    const uint64_t cap = L::capacity(rank_stride, P);
+    if (L::slice_for(cap, P, fmt) > rank_stride) return LL_ERR_SCRATCH;
+    const L::Areas ar = L::areas(cap, P, fmt);
+    last.stride = rank_stride;
+    last.P = P;
+    last.rg = Region{cap, ar.a8, ar.a128, ar.aa, ar.as, fmt};
+  }
   if (in_bytes > L::kMaxInputBytes) return LL_ERR_UNSUPPORTED;
-  if (in_bytes > cap) return LL_ERR_SCRATCH;
-  const L::Areas ar = L::areas(cap, P, fmt);
-  rg->cap = cap;
-  rg->a8 = ar.a8;
-  rg->a128 = ar.a128;
-  rg->aa = ar.aa;
-  rg->as = ar.as;
-  rg->fmt = fmt;
+  if (in_bytes > last.rg.cap) return LL_ERR_SCRATCH;
+  *rg = last.rg;
   return LL_OK;
 }
 

@@ -68,8 +68,13 @@ class SymRegion:
 
     @staticmethod
     def stream_handle(stream=None) -> int:
-        s = stream if stream is not None else torch.cuda.current_stream()
-        return s.cuda_stream
+        """The hipStream_t of `stream`, by default the current stream of the
+        current device.  The handle is asked for directly: building the
+        torch.cuda.Stream object around it took 2.7 of the 7.8 us that a small
+        call spends on the host."""
+        if stream is not None:
+            return stream.cuda_stream
+        return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
 
     # -- set-up
     def init(self, stream=None) -> None:
