@@ -972,6 +972,18 @@ int ll_slice_layout(size_t rank_stride, int nranks, size_t *offsets6) {
   return LL_OK;
 }
 
+// Zeroes bytes [lo, mid) and sets bytes [mid, hi) of every slice to the
+// sentinel (all multiples of 256): at most 8 workgroups per CU, none without
+// at least one row of 16 bytes per lane.
+static void reset_areas(char *base, size_t stride, int nranks, uint64_t lo, uint64_t mid, uint64_t hi, int cus,
+                        void *stream) {
+  if (hi <= lo) return;
+  const uint64_t most = (uint64_t)cus * 8 / (uint64_t)nranks;
+  const uint64_t x = std::max<uint64_t>(1, std::min(most, L::ceil_div(hi - lo, 256 * 16)));
+  hipLaunchKernelGGL(k_reset_areas, dim3((unsigned)x, (unsigned)nranks), dim3(256), 0, (hipStream_t)stream, base,
+                     (uint64_t)stride, lo, mid, hi);
+}
+
 int ll_init(void *sym_base, size_t rank_stride, int nranks, void *stream) {
   if (sym_base == nullptr) return LL_ERR_INVALID;
   if (nranks < 2 || nranks > LL_MAX_RANKS) return LL_ERR_INVALID;
@@ -984,12 +996,7 @@ int ll_init(void *sym_base, size_t rank_stride, int nranks, void *stream) {
   if (st != LL_OK) return st;
   // flags start at 0 (never a valid epoch); sentinel slots start at the sentinel
   const uint64_t lo = rg.cap, mid = rg.cap + rg.a8 + rg.a128 + rg.aa, hi = mid + rg.as;
-  if (mid > lo)
-    hipLaunchKernelGGL(k_fill_areas, dim3(d.cus * 4), dim3(256), 0, (hipStream_t)stream, (char *)sym_base,
-                       (uint64_t)rank_stride, nranks, lo, mid, 0u);
-  if (hi > mid)
-    hipLaunchKernelGGL(k_fill_areas, dim3(d.cus * 4), dim3(256), 0, (hipStream_t)stream, (char *)sym_base,
-                       (uint64_t)rank_stride, nranks, mid, hi, ProtoSent::kSentinel);
+  reset_areas((char *)sym_base, rank_stride, nranks, lo, mid, hi, d.cus, stream);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) {
     t_last_hip = (int)e;
@@ -1119,10 +1126,7 @@ int ll_scratch_init(void *scratch_base, size_t scratch_stride, int nranks, void 
   if (st != LL_OK) return st;
   const uint64_t mid = 2 * (L::area8(D, nranks) + L::area128(D, nranks));
   const uint64_t hi = mid + 2 * L::areaS(D, nranks);
-  hipLaunchKernelGGL(k_fill_areas, dim3(d.cus * 4), dim3(256), 0, (hipStream_t)stream, (char *)scratch_base,
-                     (uint64_t)scratch_stride, nranks, (uint64_t)0, mid, 0u);
-  hipLaunchKernelGGL(k_fill_areas, dim3(d.cus * 4), dim3(256), 0, (hipStream_t)stream, (char *)scratch_base,
-                     (uint64_t)scratch_stride, nranks, mid, hi, ProtoSent::kSentinel);
+  reset_areas((char *)scratch_base, scratch_stride, nranks, 0, mid, hi, d.cus, stream);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) {
     t_last_hip = (int)e;
