@@ -439,8 +439,12 @@ bool ring_size_ok(int mode, const Plan &pl, uint64_t total) {
 // 6.6 TB/s of reads and writes together), not by latency, from 4 waves per CU
 // on: 64 MiB at 8 ranks 312 us with 4, 308 with 8, 311 with 16; 16 MiB 84, 79
 // and 79-100.  Fewer waves also keep the ring small: 8 per CU are 56 MiB of
-// slots at 8 ranks, which stay in the memory-side cache.
-constexpr uint64_t kRingWavesPerCu = 8;
+// slots at 8 ranks, which stay in the memory-side cache.  At 2 and 3 ranks a
+// wave has only one or two peers' tiles in flight, and 16 are faster (2 ranks,
+// 16 MiB: ReduceScatter 17.1 -> 14.6 us, Broadcast 15.1 -> 12.3, Reduce 17.3 ->
+// 15.1, AllReduce 18.1 -> 17.5; 3 ranks: Broadcast 21.9 -> 19.3, AllReduce 8 MiB
+// 17.8 -> 16.8), except in the AllGather, which has no tiles to wait for.
+uint64_t ring_waves_per_cu(int mode, int P) { return P <= 3 && mode != RING_AG ? 16 : 8; }
 
 // Whether a ring kernel serves this call: no tuning field set, every stream
 // 4-byte aligned, at most kRingMaxBytes per rank (32-bit stream offsets) and a size
@@ -483,7 +487,7 @@ bool ring_launch(const Plan &pl, void *stream, int *rc) {
   if ((*rc = resident_grid(reinterpret_cast<const void *>(fn), kRingThreads, &cap)) != LL_OK) return true;
   if ((*rc = device_info(&d)) != LL_OK) return true;
   constexpr uint64_t per_wg = kRingThreads / 64;
-  const uint64_t max_wg = std::min((uint64_t)cap, kRingWavesPerCu * (uint64_t)d.cus / per_wg) / (uint64_t)P;
+  const uint64_t max_wg = std::min((uint64_t)cap, ring_waves_per_cu(mode, P) * (uint64_t)d.cus / per_wg) / (uint64_t)P;
   const uint64_t tile = pl.proto == PR_LINE ? RingTile<ProtoLine>::kPayload : RingTile<ProtoLL>::kPayload;
   L::RingShape sh;
   if (!L::ring_shape(P, mode, L::ceil_div(chunk, tile), pl.area_bytes, per_wg, max_wg, &sh)) return false;
