@@ -31,6 +31,7 @@ enum Proto { PR_LL = 0, PR_LINE = 1, PR_SENT = 2, PR_COUNT = 3 };
 constexpr int kMaxRanks = 8;
 
 typedef void (*kernel_fn)(KArgs);
+typedef void (*tile_fn)(TileArgs);
 
 struct Table {
   kernel_fn k[PR_COUNT][2][kMaxRanks + 1][K_KINDS];
@@ -39,12 +40,12 @@ struct Table {
   // two-shot, one wave per peer: [AllReduce, ReduceScatter, AllGather][log2 U][8-byte, sentinel, lines][dtype][P]
   kernel_fn twaves[3][3][3][2][kMaxRanks + 1];
   // one-shot, one tile per workgroup: [8-byte packets, sentinel, lines][dtype][P]
-  kernel_fn tile[3][2][kMaxRanks + 1];
+  tile_fn tile[3][2][kMaxRanks + 1];
   // two-shot, one tile per workgroup: [AllReduce, ReduceScatter, AllGather][log2 U][8-byte packets, sentinel,
   // lines][dtype][P]
-  kernel_fn ttile[3][2][3][2][kMaxRanks + 1];
+  tile_fn ttile[3][2][3][2][kMaxRanks + 1];
   // Broadcast / Reduce, one tile per workgroup: [8-byte packets, sentinel][Broadcast, Reduce][dtype][P]
-  kernel_fn rtile[2][2][2][kMaxRanks + 1];
+  tile_fn rtile[2][2][2][kMaxRanks + 1];
   // ring kernels: [RingMode][8-byte packets, lines][dtype][P]
   ring_fn ring[5][2][2][kMaxRanks + 1];
 };

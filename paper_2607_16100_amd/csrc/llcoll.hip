@@ -287,13 +287,13 @@ bool twoshot_tile_eligible(const Plan &pl) {
 // The one-tile kernel with 2^lu units per lane, if it can run this call:
 // every tile resident, and (unless the units per lane are forced) within the
 // waves-per-CU limit of rule 1 for one unit per lane.
-bool twoshot_tile_ok(const Plan &pl, int wpr, int lu, kernel_fn *tf, int64_t *tiles) {
+bool twoshot_tile_ok(const Plan &pl, int wpr, int lu, tile_fn *tf, int64_t *tiles) {
   if (!twoshot_tile_eligible(pl) || lu > 1) return false;
   const int mode = pl.kind == K_TWOSHOT_WAVES ? 0 : (pl.kind == K_RS_WAVES ? 1 : 2);
-  kernel_fn f = table().ttile[mode][lu][wpr][pl.dt][pl.P];
+  const tile_fn f = table().ttile[mode][lu][wpr][pl.dt][pl.P];
   int cap = 0;
   DevInfo d;
-  if (f == nullptr || resident_grid(f, 64 * pl.P, &cap) != LL_OK || device_info(&d) != LL_OK) return false;
+  if (f == nullptr || resident_grid(reinterpret_cast<const void *>(f), 64 * pl.P, &cap) != LL_OK || device_info(&d) != LL_OK) return false;
   const int64_t blocks = pl.proto == PR_LINE ? pl.units : (pl.units + 63) / 64;
   const int64_t t = (blocks + (1 << lu) - 1) >> lu;
   if (t > cap / pl.P) return false;
@@ -345,7 +345,7 @@ int wave_units_log2(const Plan &pl, int wpr) {
     return 1;
   }
   if (pl.kind != K_TWOSHOT_WAVES) return 0;
-  kernel_fn tf = nullptr;
+  tile_fn tf = nullptr;
   int64_t tiles = 0;
   if (twoshot_tile_ok(pl, wpr, 0, &tf, &tiles)) return 0;
   if (twoshot_tile_eligible(pl)) {
@@ -394,6 +394,7 @@ uint32_t clear_slots(const Plan &pl) {
 }
 
 int launch_kernel(kernel_fn fn, const Plan &pl, int W, int threads, void *stream);
+int launch_tile(tile_fn fn, const Plan &pl, int W, void *stream);
 
 // ---------------------------------------------------------------- ring kernels
 // Total bytes (all ranks' inputs; AllGather: one rank's output) from which a
@@ -546,35 +547,35 @@ int launch(const Plan &pl, void *stream) {
   // once, no forced launch shape -> the straight-line one-tile kernels.
   if (pl.kind == K_ONESHOT_WAVES && wlog == 0 && !pl.o.forced_shape() && pl.a.al4 != 0 &&
       (pl.a.in == nullptr || pl.a.in_al4 != 0) && pl.a.iters <= 1) {
-    kernel_fn tf = table().tile[pl.proto == PR_SENT ? 1 : (pl.proto == PR_LINE ? 2 : 0)][pl.dt][pl.P];
+    const tile_fn tf = table().tile[pl.proto == PR_SENT ? 1 : (pl.proto == PR_LINE ? 2 : 0)][pl.dt][pl.P];
     int cap = 0;
-    const int rc = resident_grid(tf, 64 * pl.P, &cap);
+    const int rc = resident_grid(reinterpret_cast<const void *>(tf), 64 * pl.P, &cap);
     if (rc != LL_OK) return rc;
     const int64_t tiles = pl.proto == PR_LINE ? pl.units : (pl.units + 63) / 64;
-    if (tf != nullptr && tiles <= cap / pl.P) return launch_kernel(tf, pl, (int)tiles, 64 * pl.P, stream);
+    if (tf != nullptr && tiles <= cap / pl.P) return launch_tile(tf, pl, (int)tiles, stream);
   }
   // Broadcast / Reduce with a one-lane format under the same conditions:
   // the straight-line rooted kernel (one tile of 64 units per workgroup).
   if ((pl.kind == K_BCAST || pl.kind == K_REDUCE) && pl.proto != PR_LINE && !pl.o.forced_shape() &&
       pl.a.al4 != 0 && (pl.a.in == nullptr || pl.a.in_al4 != 0)) {
-    kernel_fn tf = table().rtile[pl.proto == PR_SENT ? 1 : 0][pl.kind == K_BCAST ? 0 : 1][pl.dt][pl.P];
+    const tile_fn tf = table().rtile[pl.proto == PR_SENT ? 1 : 0][pl.kind == K_BCAST ? 0 : 1][pl.dt][pl.P];
     int cap = 0;
-    const int rc = resident_grid(tf, 64 * pl.P, &cap);
+    const int rc = resident_grid(reinterpret_cast<const void *>(tf), 64 * pl.P, &cap);
     if (rc != LL_OK) return rc;
     const int64_t tiles = (pl.units + 63) / 64;
     if (tf != nullptr && tiles <= cap / pl.P) {
       Plan tp = pl;
       tp.rooted_tile = true;
-      return launch_kernel(tf, tp, (int)tiles, 64 * pl.P, stream);
+      return launch_tile(tf, tp, (int)tiles, stream);
     }
   }
   // The same for the two-shot AllReduce and the stand-alone ReduceScatter /
   // AllGather with one unit per lane (the AllReduce with lines also two)
   // and one iteration: the straight-line two-shot kernel.
   if (two_waves) {
-    kernel_fn tf = nullptr;
+    tile_fn tf = nullptr;
     int64_t tiles = 0;
-    if (twoshot_tile_ok(pl, wpr, wlog, &tf, &tiles)) return launch_kernel(tf, pl, (int)tiles, 64 * pl.P, stream);
+    if (twoshot_tile_ok(pl, wpr, wlog, &tf, &tiles)) return launch_tile(tf, pl, (int)tiles, stream);
   }
   int threads = pl.o.threads;
   if (threads == 0) threads = 256;
@@ -631,6 +632,41 @@ int launch_kernel(kernel_fn fn, const Plan &pl, int W, int threads, void *stream
   a.phases = pl.o.phases;
   hipLaunchKernelGGL(fn, dim3(grid), dim3(threads), 0, (hipStream_t)stream, a);
   hipError_t e = hipGetLastError();
+  if (pl.o.grid_out) *pl.o.grid_out = grid;
+  if (pl.o.threads_out) *pl.o.threads_out = threads;
+  if (e != hipSuccess) {
+    t_last_hip = (int)e;
+    return LL_ERR_HIP;
+  }
+  return LL_OK;
+}
+
+// Launch a one-tile kernel: a workgroup of P waves per rank and tile.
+int launch_tile(tile_fn fn, const Plan &pl, int W, void *stream) {
+  const int grid = W * pl.P, threads = 64 * pl.P;
+  const bool inside = pl.a.in == nullptr;  // the input inside the region, at offset 0 of every slice
+  TileArgs t;
+  t.in = inside ? pl.a.sym : pl.a.in;
+  t.in_stride = inside ? pl.a.stride : pl.a.in_stride;
+  t.area = pl.a.sym + pl.a.area;
+  t.stride = pl.a.stride;
+  t.out = pl.a.out;
+  t.bytes = (uint32_t)(pl.a.n * (pl.dt == LL_BF16 ? 2 : 4));  // an input is at most 256 MiB
+  t.chunk = (uint32_t)pl.a.chunk;
+  t.slot = (uint32_t)pl.a.slot;
+  t.units = (uint32_t)pl.units;
+  t.epoch = pl.a.epoch;
+  t.misc = (uint32_t)(pl.o.mute + 1) | clear_slots(pl) << 8 | (uint32_t)pl.a.root << 16;
+  t.timeout = pl.o.timeout;
+  const int st = status_of(stream, &t.status);
+  if (st != LL_OK) return st;
+  t.stamps = pl.o.stamps;
+  t.phases = pl.o.phases;
+  t.grid = (uint32_t)grid;
+  t.first_wait = (uint16_t)pl.o.first_wait;
+  t.poll_gap = (uint16_t)pl.o.poll_gap;
+  hipLaunchKernelGGL(fn, dim3(grid), dim3(threads), 0, (hipStream_t)stream, t);
+  const hipError_t e = hipGetLastError();
   if (pl.o.grid_out) *pl.o.grid_out = grid;
   if (pl.o.threads_out) *pl.o.threads_out = threads;
   if (e != hipSuccess) {
