@@ -87,22 +87,24 @@ void fill_rtile(Table *t) {
   t->rtile[1][1][1][P] = k_rooted_tile<ProtoSent, 1, P, 1>;
 }
 
-template <class Pr, int DT, int P>
+template <class Pr, int DT, int P, bool Odd>
 void fill_ring(Table *t) {
   constexpr int pr = std::is_same<Pr, ProtoLine>::value ? 1 : 0;
-  t->ring[RING_AR][pr][DT][P] = k_ring<Pr, DT, P, RING_AR>;
-  t->ring[RING_RS][pr][DT][P] = k_ring<Pr, DT, P, RING_RS>;
-  t->ring[RING_AG][pr][DT][P] = k_ring<Pr, DT, P, RING_AG>;
-  t->ring[RING_BCAST][pr][DT][P] = k_ring<Pr, DT, P, RING_BCAST>;
-  t->ring[RING_REDUCE][pr][DT][P] = k_ring<Pr, DT, P, RING_REDUCE>;
+  t->ring[RING_AR][pr][DT + Odd][P] = k_ring<Pr, DT, P, RING_AR, Odd>;
+  t->ring[RING_RS][pr][DT + Odd][P] = k_ring<Pr, DT, P, RING_RS, Odd>;
+  t->ring[RING_AG][pr][DT + Odd][P] = k_ring<Pr, DT, P, RING_AG, Odd>;
+  t->ring[RING_BCAST][pr][DT + Odd][P] = k_ring<Pr, DT, P, RING_BCAST, Odd>;
+  t->ring[RING_REDUCE][pr][DT + Odd][P] = k_ring<Pr, DT, P, RING_REDUCE, Odd>;
 }
 
 template <int P>
 void fill(Table *t) {
-  fill_ring<ProtoLL, 0, P>(t);
-  fill_ring<ProtoLL, 1, P>(t);
-  fill_ring<ProtoLine, 0, P>(t);
-  fill_ring<ProtoLine, 1, P>(t);
+  fill_ring<ProtoLL, 0, P, false>(t);
+  fill_ring<ProtoLL, 1, P, false>(t);
+  fill_ring<ProtoLL, 1, P, true>(t);
+  fill_ring<ProtoLine, 0, P, false>(t);
+  fill_ring<ProtoLine, 1, P, false>(t);
+  fill_ring<ProtoLine, 1, P, true>(t);
   fill_row<ProtoLL, 0, P>(t->k[PR_LL][0][P]);
   fill_row<ProtoLL, 1, P>(t->k[PR_LL][1][P]);
   fill_row<ProtoLine, 0, P>(t->k[PR_LINE][0][P]);

@@ -129,7 +129,12 @@ __device__ __forceinline__ RingArgs pin_args(const RingArgs &k) {
   return a;
 }
 
-template <class Pr, int DT, int P, int Mode>
+// Odd: streams with an odd number of bfloat16 elements.  Rows then start on
+// half a word for every other rank, which 16-byte buffer accesses take at some
+// cost (a copy with such stores runs at two thirds of the speed), and end in
+// half a word, which goes as 2 bytes of its own so that nothing outside the
+// row is read or written.
+template <class Pr, int DT, int P, int Mode, bool Odd>
 __global__ __launch_bounds__(kRingThreads) void k_ring(RingArgs ka) {
   const RingArgs a = pin_args(ka);
   const uint64_t t_start = a.stamps != nullptr ? now_ticks() : 0;
@@ -158,17 +163,50 @@ __global__ __launch_bounds__(kRingThreads) void k_ring(RingArgs ka) {
   char *const slice_r = a.sym + (uint64_t)r * a.stride;
   const rsrc_t ring_rs = make_rsrc(slice_r + a.area, (P - 1) * a.slot);
   const uint32_t my_chunk = r * a.chunk;
-  const uint32_t my_end = my_chunk + a.chunk < a.total ? my_chunk + a.chunk : a.total;
+  const uint32_t my_end = my_chunk + a.chunk < a.total ? my_chunk + a.chunk : (my_chunk < a.total ? a.total : my_chunk);
   WaitBudget budget(a.timeout, a.status);
   bool dead = false;  // a wait has expired: the wave waits no more
 
-  auto load_tile = [&](uint32_t off) -> u32x4 {
-    if constexpr (NW == 2) {
-      const u32x2 w = __builtin_amdgcn_raw_buffer_load_b64(in_rs, (int)(po + off), 0, 0);
-      return u32x4{w.x, w.y, 0u, 0u};
+  auto chunk_len = [&](uint32_t c) -> uint32_t {
+    const uint32_t at = c * a.chunk;
+    return at >= a.total ? 0u : (a.total - at < a.chunk ? a.total - at : a.chunk);
+  };
+  // Odd: which of the lane's words at byte `at` of a chunk of `len` bytes is the
+  // half word at its end (0..NW-1); NW or more: none.
+  auto tail_word = [&](uint32_t len, uint32_t at) -> uint32_t {
+    return (len & 2u) != 0 && po != kNowhere ? ((len & ~3u) - (po + at)) / 4 : kNowhere;
+  };
+  // The lane's words at byte `at` of chunk c of the rank's input (AllGather: of
+  // its input).
+  auto load_tile = [&](uint32_t c, uint32_t at) -> u32x4 {
+    u32x4 v = {0u, 0u, 0u, 0u};
+    rsrc_t rs = in_rs;
+    uint32_t off = po + at, len = 0;
+    if constexpr (Odd) {
+      len = Mode == RING_AG ? a.chunk : chunk_len(c);
+      rs = make_rsrc(a.in + (uint64_t)r * a.in_stride + (Mode == RING_AG ? 0 : (uint64_t)c * a.chunk), len & ~3u);
     } else {
-      return __builtin_amdgcn_raw_buffer_load_b128(in_rs, (int)(po + off), 0, 0);
+      off += Mode == RING_AG ? 0 : c * a.chunk;
     }
+    if constexpr (NW == 2) {
+      const u32x2 w = __builtin_amdgcn_raw_buffer_load_b64(rs, (int)off, 0, 0);
+      v.x = w.x;
+      v.y = w.y;
+    } else {
+      v = __builtin_amdgcn_raw_buffer_load_b128(rs, (int)off, 0, 0);
+    }
+    if constexpr (Odd) {
+      const uint32_t j = tail_word(len, at);
+      const rsrc_t rt = make_rsrc(a.in + (uint64_t)r * a.in_stride + (Mode == RING_AG ? 0 : (uint64_t)c * a.chunk), len);
+      const uint32_t h = __builtin_amdgcn_raw_buffer_load_b16(rt, (int)(j < NW ? len - 2 : kNowhere), 0, 0);
+      v.x = j == 0 ? h : v.x;
+      v.y = j == 1 ? h : v.y;
+      if constexpr (NW == 4) {
+        v.z = j == 2 ? h : v.z;
+        v.w = j == 3 ? h : v.w;
+      }
+    }
+    return v;
   };
   auto flag_of = [&](uint32_t s) -> uint32_t {
     return Mode == RING_BCAST ? a.epoch : a.epoch - ((s / kRingEntries) & 1u);
@@ -181,14 +219,24 @@ __global__ __launch_bounds__(kRingThreads) void k_ring(RingArgs ka) {
   // The result of the wave's tile at byte `at` of chunk r, to its output(s).
   auto store_out = [&](uint32_t at, u32x4 v) {
     v = Pr::start_store(v, sub);
-    const int off = (int)(po + my_chunk + at);
+    const uint32_t j = Odd ? tail_word(my_end - my_chunk, at) : 0;
+    const uint32_t half = j == 0 ? v.x : (j == 1 ? v.y : (j == 2 ? v.z : v.w));
 #pragma unroll
     for (int k = 0; k < P; ++k) {
       const uint32_t q = (r + k) % P;
       if (Mode == RING_RS && k > 0) break;
       if (Mode == RING_REDUCE && k > 0) break;
       const uint32_t to = Mode == RING_REDUCE ? a.root : q;
-      const rsrc_t rd = make_rsrc(a.out + (uint64_t)to * a.out_pitch, publish || to == r ? my_end : 0u);
+      const bool to_it = publish || to == r;
+      // Odd: the resource starts at the chunk, so that its whole words count
+      // from there
+      char *const row = a.out + (uint64_t)to * a.out_pitch + (Odd ? my_chunk : 0u);
+      const uint32_t end = my_end - (Odd ? my_chunk : 0u);
+      const int off = (int)(po + at + (Odd ? 0u : my_chunk));
+      const rsrc_t rd = make_rsrc(row, to_it ? (Odd ? end & ~3u : end) : 0u);
+      if constexpr (Odd)
+        __builtin_amdgcn_raw_buffer_store_b16((uint16_t)half, make_rsrc(row, to_it ? end : 0u),
+                                              (int)(j < NW ? end - 2 : kNowhere), 0, kOut);
       if constexpr (NW == 2) {
         __builtin_amdgcn_raw_buffer_store_b64(u32x2{v.x, v.y}, rd, off, 0, kOut);
       } else {
@@ -200,7 +248,7 @@ __global__ __launch_bounds__(kRingThreads) void k_ring(RingArgs ka) {
   if constexpr (Mode == RING_AG) {
     for (uint32_t s = 0; s < steps; ++s) {
       const uint32_t at = (g + s * G) * TB;
-      store_out(at, Pr::finish_load(load_tile(at), sub));
+      store_out(at, Pr::finish_load(load_tile(r, at), sub));
     }
   } else {
     u32x4 own = {0u, 0u, 0u, 0u};
@@ -213,7 +261,7 @@ __global__ __launch_bounds__(kRingThreads) void k_ring(RingArgs ka) {
         __builtin_amdgcn_s_setprio(3);
         u32x4 x[P];  // x[k]: the tile of chunk (r + k) % P
 #pragma unroll
-        for (int k = 0; k < P; ++k) x[k] = load_tile((r + k) % P * a.chunk + at);
+        for (int k = 0; k < P; ++k) x[k] = load_tile((r + k) % P, at);
         // The ring position goes into the vector offset, not into a scalar
         // offset register: with one, the compiler lets the instruction after a
         // 16-byte buffer store overwrite the store's data registers, and the

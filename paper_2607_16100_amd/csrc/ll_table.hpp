@@ -46,8 +46,8 @@ struct Table {
   tile_fn ttile[3][2][3][2][kMaxRanks + 1];
   // Broadcast / Reduce, one tile per workgroup: [8-byte packets, sentinel][Broadcast, Reduce][dtype][P]
   tile_fn rtile[2][2][2][kMaxRanks + 1];
-  // ring kernels: [RingMode][8-byte packets, lines][dtype][P]
-  ring_fn ring[5][2][2][kMaxRanks + 1];
+  // ring kernels: [RingMode][8-byte packets, lines][binary32, bfloat16, bfloat16 with odd streams][P]
+  ring_fn ring[5][2][3][kMaxRanks + 1];
 };
 
 // Defined in the unit built for that rank count.

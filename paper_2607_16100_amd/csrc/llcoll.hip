@@ -447,8 +447,7 @@ bool ring_size_ok(int mode, const Plan &pl, uint64_t total) {
 // 17.8 -> 16.8), except in the AllGather, which has no tiles to wait for.
 uint64_t ring_waves_per_cu(int mode, int P) { return P <= 3 && mode != RING_AG ? 16 : 8; }
 
-// Whether a ring kernel serves this call: no tuning field set, every stream
-// 4-byte aligned, at most kRingMaxBytes per rank (32-bit stream offsets) and a size
+// Whether a ring kernel serves this call: no tuning field set, at most kRingMaxBytes per rank (32-bit stream offsets) and a size
 // for which it is the faster one.  Otherwise the call's other kernel runs.
 bool ring_serves(const Plan &pl, int *mode_out, uint64_t *total_out, uint64_t *chunk_out) {
   int mode;
@@ -464,7 +463,6 @@ bool ring_serves(const Plan &pl, int *mode_out, uint64_t *total_out, uint64_t *c
   if (pl.proto == PR_SENT || o.forced_shape() || o.wave_units != 0 || o.wave_kernels != 0 || o.clear_slots != 0 ||
       o.lag != 1 || o.first_wait != 0 || o.poll_gap != 0 || o.phases != nullptr)
     return false;
-  if (pl.a.al4 == 0 || (pl.a.in != nullptr && pl.a.in_al4 == 0)) return false;
   const int es = pl.dt == LL_BF16 ? 2 : 4;
   const bool blocks = mode == RING_RS || mode == RING_AG;  // P chunks of n elements
   const uint64_t total = (uint64_t)pl.a.n * (uint64_t)es * (blocks ? (uint64_t)pl.P : 1);
@@ -482,7 +480,8 @@ bool ring_launch(const Plan &pl, void *stream, int *rc) {
   uint64_t total, chunk;
   if (!ring_serves(pl, &mode, &total, &chunk)) return false;
   const int P = pl.P;
-  const ring_fn fn = table().ring[mode][pl.proto == PR_LINE ? 1 : 0][pl.dt][P];
+  const int odd = pl.a.al4 == 0 || (pl.a.in != nullptr && pl.a.in_al4 == 0) ? 1 : 0;  // bfloat16 only
+  const ring_fn fn = table().ring[mode][pl.proto == PR_LINE ? 1 : 0][pl.dt + odd][P];
   int cap = 0;
   DevInfo d;
   if ((*rc = resident_grid(reinterpret_cast<const void *>(fn), kRingThreads, &cap)) != LL_OK) return true;
@@ -1275,9 +1274,9 @@ static int buffered_call(const void *in, void *out, size_t count, ll_dtype dt, l
     if (iters > 1 && algo == LL_ALGO_ONESHOT_WAVES) algo = LL_ALGO_TWOSHOT_WAVES;
     if (iters > 1 && algo == LL_ALGO_ONESHOT_SENTINEL_WAVES) algo = LL_ALGO_TWOSHOT_SENTINEL_WAVES;
     if (iters > 1 && algo == LL_ALGO_ONESHOT_LINE_WAVES) algo = LL_ALGO_TWOSHOT_LINE_WAVES;
-    // several iterations of whole words: the ring kernels (ring_serves), with
+    // several iterations: the ring kernels (ring_serves), with
     // lines unless the call forbids them
-    if (iters > 1 && in_bytes % 4 == 0 && in_bytes <= L::kRingMaxBytes)
+    if (iters > 1 && in_bytes <= L::kRingMaxBytes)
       algo = o.lines_ok() ? LL_ALGO_TWOSHOT_LINE_WAVES : LL_ALGO_TWOSHOT_WAVES;
   }
   if (iters > 1 && is_wave_algo(algo))
@@ -1471,7 +1470,7 @@ int ll_allgather_ex(void *sym_base, size_t rank_stride, void *out, size_t sendco
     // from the size where the ring AllGather runs, its packets carry no data
     // and no format is faster than lines (8 ranks, 128 KiB per rank sent: 4.7
     // us, sentinel units 6.4)
-    const bool ring = in_bytes % 4 == 0 && in_bytes * nranks >= (nranks >= 4 ? 128u << 10 : 256u << 10);
+    const bool ring = in_bytes * nranks >= (nranks >= 4 ? 128u << 10 : 256u << 10);
     proto = proto_choice(auto_proto(in_bytes * nranks, nranks, o.sentinel_ok() && !ring, true), auto_formats(rg.fmt, o));
     if (proto == LL_PROTO_AUTO) return LL_ERR_SCRATCH;
   }

@@ -120,15 +120,24 @@ def test_named_formats_and_many_steps(op, proto):
         check(reg, op, n, p, dtype, 5, True, f"{op} {proto} call {k}", **kw)
 
 
-@pytest.mark.parametrize("p", [3, 8])
-def test_streams_that_start_on_half_a_word_run_elsewhere(p):
-    """An odd bfloat16 count puts every other output on half a word: those
-    calls keep their kernel."""
-    n = 8 * MIB // 2 + 1
-    reg = SymRegion(p, n, "bf16", out_elems=p * n + 4096)
+@pytest.mark.parametrize("op", list(FIRST))
+@pytest.mark.parametrize("p", [2, 3, 6, 7, 8])
+def test_streams_that_start_and_end_on_half_a_word(op, p):
+    """Odd bfloat16 counts: rows of odd ranks start on half a word, and a
+    stream's last element is half of one.  The half word at every place of a
+    lane, at a tile's and a chunk's first and last word, and in 8-byte packets."""
+    unit = p if op == "reduce_scatter" else 1
+    base = -(-FIRST[op](p) // 2 // unit) | 1  # elements of a chunk (ReduceScatter) or of the message
+    tile = 480 * (1 if op in ("allgather", "reduce_scatter") else p)
+    top = base // tile * tile + 3 * tile
+    counts = [base, base + 2, base + 4, base + 6, top - 1, top + 1]
+    reg = SymRegion(p, (top + 8) * unit, "bf16", out_elems=out_elems(op, p, (top + 8) * unit) + 4096)
     reg.init()
-    check(reg, "allreduce", n, p, "bf16", 0, False, f"odd count P={p}")
-    check(reg, "allreduce", n - 1, p, "bf16", 0, True, f"even count P={p}")
+    for m in counts:
+        check(reg, op, m * unit, p, "bf16", p - 1, True, f"{op} P={p} odd count {m}")
+    kw = {"algo": "twoshot_waves"} if op == "allreduce" else {"proto": "packet8"}
+    for m in (counts[0], counts[1]):
+        check(reg, op, m * unit, p, "bf16", 0, True, f"{op} P={p} odd count {m} packet8", **kw)
 
 
 def test_ring_and_other_kernels_share_a_region():
@@ -157,14 +166,17 @@ def test_ring_and_other_kernels_share_a_region():
 
 
 @pytest.mark.parametrize("in_place", [False, True])
-@pytest.mark.parametrize("p,dtype,iter_bytes", [(2, "f32", 4096), (5, "bf16", 8192), (7, "f32", 20000), (8, "bf16", 1 << 18)])
+@pytest.mark.parametrize("p,dtype,iter_bytes", [(2, "f32", 4096), (5, "bf16", 8192), (7, "f32", 20000), (8, "bf16", 1 << 18),
+                                                (3, "odd", 6000), (8, "odd", 1 << 18)])
 def test_bounded_scratch_goes_round_the_ring(p, dtype, iter_bytes, in_place):
     """Scratch regions that hold a few waves' rings: dozens to hundreds of
     steps, two calls, from epoch 1."""
+    odd = 1 if dtype == "odd" else 0
+    dtype = "bf16" if odd else dtype
     es = ES[dtype]
-    n = 120 * iter_bytes // es + 2
+    n = 120 * iter_bytes // es + 2 + odd
     if iter_bytes > 65536:
-        n = 9 * iter_bytes // es + 14
+        n = 9 * iter_bytes // es + 14 + odd
     reg = ScratchRegion(p, n, dtype, iter_bytes=iter_bytes, in_place=in_place)
     reg.init()
     for k, algo in enumerate(("auto", "twoshot_waves", "twoshot_line", "auto")):
