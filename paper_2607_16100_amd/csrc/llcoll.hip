@@ -410,10 +410,10 @@ int launch_tile(tile_fn fn, const Plan &pl, int W, void *stream);
 //  - ReduceScatter: 32 MiB (8 ranks: 2 MiB per rank 12.6 against 9.7, 4 MiB
 //    17.5 against 17.8, 8 MiB 33.2 against 36.3; 4 ranks: 4 MiB 10.3 against
 //    9.3, 8 MiB 16.8 against 19.1).
-//  - AllGather: 128 KiB of output per rank from 4 ranks up, 256 KiB below (8
-//    ranks: 64 KiB 3.03 against 2.91, 128 KiB 2.97 against 3.09, 2 MiB 6.26
-//    against 11.8, 16 MiB 26.4 against 67.4; 2 ranks: 128 KiB 2.73 against
-//    2.61, 256 KiB 2.70 against 2.94).
+//  - AllGather: 256 KiB of output per rank, up to which the one-tile kernel
+//    serves (8 ranks: 224 KiB 3.22 us against 3.25, 256 KiB 3.11 against 3.84, 2
+//    MiB 6.26 against 11.8, 16 MiB 26.4 against 67.4; 4 ranks: 128 KiB 2.98
+//    against 2.82, 256 KiB 2.99 against 3.19).
 //  - Broadcast, Reduce (bytes per rank): at 8 ranks, a rank per XCD, 128 KiB
 //    (Broadcast 64 KiB 4.62 against 3.90, 128 KiB 4.89 against 5.08, 4 MiB
 //    12.4 against 39.6; Reduce 4.78 against 5.24 and 18.0 against 38.4).  At
@@ -424,13 +424,15 @@ int launch_tile(tile_fn fn, const Plan &pl, int W, void *stream);
 // A bounded-scratch call of several iterations always does: it would pay two
 // exchanges per iteration (32 MiB at 8 ranks in 1 MiB iterations 345 -> 161
 // us, in 256 KiB iterations 540 -> 219 us).
+constexpr uint64_t kRingAllGatherBytes = 256u << 10;
+
 bool ring_size_ok(int mode, const Plan &pl, uint64_t total) {
   const uint64_t KiB = 1024, MiB = 1024 * 1024;
   const int P = pl.P;
   switch (mode) {
     case RING_AR: return pl.a.iters > 1 || total * P >= (pl.proto == PR_LINE ? 7 : 5) * MiB;
     case RING_RS: return total * P >= 32 * MiB;
-    case RING_AG: return total >= (P >= 4 ? 128 : 256) * KiB;
+    case RING_AG: return total >= kRingAllGatherBytes;
     case RING_BCAST: return total >= (P == 8 ? 128 * KiB : (P >= 4 ? 1 * MiB : 4 * MiB));
     default: return total >= (P == 8 ? 128 * KiB : (P >= 4 ? 2 * MiB : 16 * MiB));
   }
@@ -1470,7 +1472,7 @@ int ll_allgather_ex(void *sym_base, size_t rank_stride, void *out, size_t sendco
     // from the size where the ring AllGather runs, its packets carry no data
     // and no format is faster than lines (8 ranks, 128 KiB per rank sent: 4.7
     // us, sentinel units 6.4)
-    const bool ring = in_bytes * nranks >= (nranks >= 4 ? 128u << 10 : 256u << 10);
+    const bool ring = in_bytes * nranks >= kRingAllGatherBytes;
     proto = proto_choice(auto_proto(in_bytes * nranks, nranks, o.sentinel_ok() && !ring, true), auto_formats(rg.fmt, o));
     if (proto == LL_PROTO_AUTO) return LL_ERR_SCRATCH;
   }

@@ -73,7 +73,7 @@ def check(reg, op, n, p, dtype, root, ring, what, opt=None, **kw):
 # (operation, first size per rank in bytes on the ring, by rank count)
 FIRST = {
     "allreduce": lambda p: -(-7 * MIB // p), "reduce_scatter": lambda p: -(-32 * MIB // p),
-    "allgather": lambda p: -(-(128 if p >= 4 else 256) * KIB // p),
+    "allgather": lambda p: -(-256 * KIB // p),
     "broadcast": lambda p: 128 * KIB if p == 8 else (MIB if p >= 4 else 4 * MIB),
     "reduce": lambda p: 128 * KIB if p == 8 else (2 * MIB if p >= 4 else 16 * MIB),
 }
