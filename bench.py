@@ -59,7 +59,7 @@ def kernel_source_hash() -> str:
     left out: a counter summary stays valid across comment edits."""
     h = hashlib.sha256()
     csrc = os.path.join(ROOT, "paper_2607_16100_amd", "csrc")
-    for name in ("ll_device.hpp", "ll_kernels.hpp", "ll_layout.hpp", "ll_iter.hpp"):
+    for name in ("ll_device.hpp", "ll_kernels.hpp", "ll_layout.hpp", "ll_iter.hpp", "ll_ring.hpp"):
         with open(os.path.join(csrc, name), encoding="utf-8") as f:
             h.update(name.encode())
             h.update(_code_only(f.read()).encode())
@@ -483,7 +483,6 @@ def bench_sweep(torch, ll, path, floor_p50_us=None):
     """C4: 8 ranks, binary32, 2 .. 2^26 elements per rank; p50/p99 and GB/s of
     every algorithm at every size (written to `path` as JSON lines), each with
     its ratio to the latency floor and its fraction of the HBM peak."""
-    from paper_2607_16100_amd import bytemodel
     from paper_2607_16100_amd.region import SymRegion
 
     p = 8
@@ -509,7 +508,7 @@ def bench_sweep(torch, ll, path, floor_p50_us=None):
                 if algo in ("twoshot_atomic", "twoshot_sentinel_out") and n < 4:
                     continue
                 r = paced_collective(torch, ll, reg, "ar", n, ll.ALGOS[algo], steps, min(20, steps))
-                gbps = (bytemodel.allreduce_bytes(algo, p, n, 4) / r["p50_us"] / 1e3) if algo != "auto" else None
+                gbps = (moved_bytes(algo, p, n, 4) / r["p50_us"] / 1e3) if algo != "auto" else None
                 b = bound_us(floor_p50_us, p, n, 4)
                 r.update({"elements": n, "bytes_per_rank": n * 4, "algo": algo, "algorithmic_gbps_p50": gbps,
                           "hbm_frac_p50": gbps / PEAK_HBM_GBS if gbps else None,
@@ -552,6 +551,21 @@ def bench_sol_pieces(torch, ll):
     }
 
 
+RING_MIN_BYTES = {"line128": 7 << 20, "packet8": 5 << 20}  # all ranks' inputs from which a two-shot runs on the ring
+
+
+def moved_bytes(algo, p, count, esize):
+    """The algorithmic bytes of one AllReduce call: the flagged two-shot
+    algorithms run on the ring kernels at the bandwidth-bound sizes."""
+    from paper_2607_16100_amd import bytemodel
+
+    if algo in ("twoshot", "twoshot_line", "twoshot_waves", "twoshot_line_waves"):
+        proto = "line128" if "_line" in algo else "packet8"
+        if p * count * esize >= RING_MIN_BYTES[proto]:
+            return bytemodel.ring_allreduce_bytes(proto, p, count, esize)
+    return bytemodel.allreduce_bytes(algo, p, count, esize)
+
+
 def bench_bandwidth(torch, ll, count, algos, iters=20, warmup=3):
     """Average kernel time (HIP events on the launch stream) and GB/s at `count`
     binary32 elements per rank, 8 ranks."""
@@ -586,7 +600,7 @@ def bench_bandwidth(torch, ll, count, algos, iters=20, warmup=3):
         torch.cuda.synchronize()
         ll.check(ll.ll_check(stream.cuda_stream), algo)
         us = ev0.elapsed_time(ev1) * 1000.0 / iters
-        nbytes = bytemodel.allreduce_bytes(algo, p, count, 4)
+        nbytes = moved_bytes(algo, p, count, 4)
         useful = bytemodel.useful_bytes(p, count, 4)
         grid, threads = shape.grid, shape.threads
         res[algo] = {"kernel_us": us, "algorithmic_bytes": nbytes, "gbps": nbytes / us / 1e3,
@@ -711,10 +725,10 @@ def bench_cpu_all_cores(seconds: float):
 
 
 # The 64 MiB leg's kernel: what AUTO runs for 64 MiB of binary32 per rank at 8
-# ranks (the line two-shot with one wave per peer, four units per lane).
+# ranks (the line two-shot on the ring kernel).
 BW_ALGO = "twoshot_line_waves"
-BW_KERNEL = "k_twoshot_waves<ProtoLine, f32, 8, 4> (64 MiB per rank, 8 ranks)"
-BW_COUNTERS = "twoshot_line_waves_f32_64MiB_p8_counters.txt"
+BW_KERNEL = "k_ring<ProtoLine, f32, 8, AllReduce> (64 MiB per rank, 8 ranks)"
+BW_COUNTERS = "ring_f32_64MiB_p8_counters.txt"
 
 
 def traffic_from_profiles(kernel_hash: str, grid_threads: int):

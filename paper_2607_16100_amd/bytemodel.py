@@ -59,6 +59,16 @@ def allreduce_bytes(algo: str, p: int, count: int, esize: int) -> float:
     return p * per_rank
 
 
+def ring_allreduce_bytes(proto: str, p: int, count: int, esize: int) -> float:
+    """Bytes of a two-shot AllReduce on the ring kernels: the owner of a
+    reduced chunk stores it straight into every output, so only the
+    ReduceScatter's packets are written and read back (in positions that are
+    reused, which keeps them in the memory-side cache)."""
+    m = count * esize
+    c = math.ceil(count / p) * esize
+    return p * (m + COPY_FACTOR[proto] * (p - 1) * c + m)
+
+
 def twoshot_sentinel_out_bytes(p: int, count: int, esize: int) -> float:
     """Two-shot sentinel with the AllGather stored into the peers' outputs:
     per rank, the input M, the ReduceScatter's (P-1) chunk copies (written,
