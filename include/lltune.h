@@ -22,7 +22,9 @@ extern "C" {
 /* Launch-shape and test hooks of one call (ll_options.tuning).  Results never
  * depend on the launch-shape fields; the test hooks change only what they
  * name.  Fill with ll_tuning_init (every field off / automatic), then set
- * fields. */
+ * fields.  The ring kernels of the bandwidth-bound sizes have none of the
+ * launch-shape, pacing, clearing and phase hooks: a call that sets one runs on
+ * the kernel that has it. */
 struct ll_tuning {
   uint32_t size;            /* sizeof(ll_tuning), set by ll_tuning_init */
   int workgroups_per_rank;  /* 0 = automatic; never more than can be resident */
