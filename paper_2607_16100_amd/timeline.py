@@ -49,7 +49,10 @@ def run_case(p: int, n: int, dtype: str, algo: str, calls: int, phases=PHASES):
     reg.init()
     reg.write_inputs(x)
     s = reg.stream_handle()
-    shape = ll.Options(report=True)
+    # the launch shape of a call that records phases (one that does not may run
+    # on another kernel); 4 words for each wave of the largest grid there is
+    warm = torch.zeros(4 * 256 * 32, dtype=torch.int64, device="cuda")
+    shape = ll.Options(report=True, phases=warm.data_ptr())
     for _ in range(50):
         ll.check(reg.allreduce(n, algo, opt=shape))
     torch.cuda.synchronize()
