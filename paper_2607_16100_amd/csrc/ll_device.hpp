@@ -47,8 +47,12 @@ __device__ __forceinline__ rsrc_t make_rsrc(const void *base, uint32_t bytes) {
 __device__ __forceinline__ void st_pkt(rsrc_t rs, uint32_t off, u32x4 v) {
   __builtin_amdgcn_raw_buffer_store_b128(v, rs, (int)off, 0, kSC1);
 }
+// The slot's offset is added to the vector offset and not passed in a scalar
+// register: with one, the compiler lets the instruction after the store
+// overwrite the data registers, and the store's last lanes have then carried
+// the new contents (seen in a ring kernel's packet stores).
 __device__ __forceinline__ void st_pkt_at(rsrc_t rs, uint32_t off, uint32_t soff, u32x4 v) {
-  __builtin_amdgcn_raw_buffer_store_b128(v, rs, (int)off, (int)soff, kSC1);
+  __builtin_amdgcn_raw_buffer_store_b128(v, rs, (int)(off + soff), 0, kSC1);
 }
 __device__ __forceinline__ u32x4 ld_pkt(rsrc_t rs, uint32_t off, uint32_t soff = 0) {
   return __builtin_amdgcn_raw_buffer_load_b128(rs, (int)off, (int)soff, kSC1);

@@ -14,7 +14,7 @@
 //    ranks moves 3.3 GB with it and 2.1 GB without.
 //  - A ring of packets.  A wave reuses kRingEntries positions of 1 KiB per
 //    peer instead of a slot position per tile, so the packets of a call of any
-//    size live in at most 56 MiB at 8 ranks and never reach HBM.  Each peer's
+//    size live in at most 56 MiB at 8 ranks, which that cache can hold.  Each peer's
 //    packets are the credit to go on (see kRingEntries), so a ring needs no
 //    counter, no barrier and no second buffer; a bounded-scratch call needs no
 //    iterations.
@@ -24,7 +24,7 @@
 // Measured (8 ranks, bfloat16 unless said, against the kernels that pass the
 // result through scratch): AllReduce 1 MiB 10.7 -> 9.2 us, 4 MiB 31.1 -> 22,
 // 16 MiB 124 -> 79, 64 MiB of binary32 500 -> 308; AllGather 448 KiB sent
-// 17.7 -> 8.1; Broadcast 16 MiB 146 -> 67; Reduce 16 MiB 146 -> 65; bounded
+// 17.7 -> 8.1; Broadcast 16 MiB 146 -> 42; Reduce 16 MiB 146 -> 65; bounded
 // scratch, 32 MiB in 1 MiB iterations 345 -> 161.
 //
 // Grid = P * W workgroups of kRingThreads threads; workgroup b serves rank
