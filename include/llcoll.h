@@ -49,7 +49,9 @@
  *
  * Epochs.  The flag carried by every packet is the caller's `epoch`, which
  * must be >= 1 and must strictly increase over all calls on one region (any
- * entry point); 0 marks zeroed scratch (ll_init).  Sentinel-mode calls check
+ * entry point); 0 marks zeroed scratch (ll_init), and where a large call
+ * reuses a packet position, every other packet there, which no other call
+ * accepts.  A call writes no other call's epoch.  Sentinel-mode calls check
  * the epoch like the others but do not use it.  After epoch 0xFFFFFFFF,
  * call ll_init again and restart at 1.  (The paper's buffer object keeps this
  * counter internally and advances it itself, Sec. V; here the caller owns it.)

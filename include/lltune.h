@@ -92,6 +92,11 @@ int ll_iteration_span(size_t count, size_t iter_count, uint32_t it, int nranks, 
 int ll_ring_shape(int nranks, int mode, uint64_t tiles, uint64_t area_bytes, uint64_t per_wg, uint64_t max_wg,
                   uint64_t *out4);
 
+/* The flag that a ring kernel's packets of step `step` carry in a call with
+ * this epoch (Broadcast, whose packets all have positions of their own, uses
+ * the epoch alone).  Host only. */
+uint32_t ll_ring_flag(uint32_t epoch, uint32_t step);
+
 #ifdef __cplusplus
 }
 #endif

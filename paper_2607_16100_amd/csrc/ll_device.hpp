@@ -8,7 +8,9 @@
 //     which payload word goes where is chosen so that every access to the
 //     input and output is 16-byte aligned (ProtoLine below).
 // The flag is the call's epoch.  A receiver accepts a packet once every flag
-// covering it equals the epoch; zeroed scratch (flag 0) never matches.
+// covering it equals the epoch; zeroed scratch (flag 0) never matches.  (The
+// ring kernels also send packets with flag 0, over packets that their receiver
+// has accepted; see ll_ring.hpp.)
 //
 // Cross-XCD visibility without fences: every packet store and every poll
 // load carries the sc1 cache-policy bit (agent scope), which is how the
@@ -43,7 +45,7 @@ __device__ __forceinline__ rsrc_t make_rsrc(const void *base, uint32_t bytes) {
 
 // Coherent 16-byte packet store / load.  Offsets past the resource's size are
 // discarded (store) or read as zero (load), so a wrong offset can never touch
-// memory outside the slot; a zero flag is never accepted.
+// memory outside the slot; no epoch equals the zero flag read there.
 __device__ __forceinline__ void st_pkt(rsrc_t rs, uint32_t off, u32x4 v) {
   __builtin_amdgcn_raw_buffer_store_b128(v, rs, (int)off, 0, kSC1);
 }

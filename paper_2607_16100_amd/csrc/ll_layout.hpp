@@ -149,6 +149,11 @@ inline uint64_t capacity(uint64_t stride, int P) {
 // than the tiles need when every wave takes the same number of steps.
 constexpr uint64_t kRingEntries = 4;
 constexpr uint64_t kRingPacketBytes = 1024, kRingFlagBytes = 64;
+// Flag of the packets of a wave's step: the call's epoch and 0 in turn on each
+// position.  Both are the call's own, since 0 is no call's epoch.
+constexpr uint32_t ring_flag(uint32_t epoch, uint32_t step) {
+  return ((step / (uint32_t)kRingEntries) & 1u) != 0 ? 0u : epoch;
+}
 // 32-bit stream offsets with the top bit free for "nowhere" (ll_ring.hpp)
 constexpr uint64_t kRingMaxBytes = (2ull << 30) - (1ull << 20);
 enum RingMode { RING_AR = 0, RING_RS = 1, RING_AG = 2, RING_BCAST = 3, RING_REDUCE = 4 };

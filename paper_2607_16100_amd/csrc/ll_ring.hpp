@@ -62,10 +62,13 @@ using layout::RING_RS;
 // reduced tile s - 4: position s % 4 has been read and is free again.
 //
 // The flag must tell a position's tiles apart although the caller gives a
-// call one epoch: the tiles of a position carry the epoch and the epoch less
-// one in turn.  The first time round a position holds an older flag, below the
-// epoch; from then on it holds the other value of the two, because its reader
-// has seen it there.  Neither value can be taken for a later call's epoch.
+// call one epoch: the tiles of a position carry the epoch and 0 in turn
+// (layout::ring_flag).  The first time round a position holds another call's
+// flag or 0, neither of which is the epoch; from then on it holds the other
+// value of the two, because its reader has seen it there, so a 0 is never
+// waited for where one was left before the call.  Neither value can be taken
+// for another call's epoch, whichever of the two calls runs first: a call
+// captured into a graph runs after calls that were given later epochs.
 constexpr uint32_t kRingEntries = (uint32_t)layout::kRingEntries;
 static_assert(kRingEntries == 4, "a publish one step ahead needs four positions");
 // Waves are independent; two to a workgroup spread a 1 MiB call over the CUs
@@ -209,7 +212,7 @@ __global__ __launch_bounds__(kRingThreads) void k_ring(RingArgs ka) {
     return v;
   };
   auto flag_of = [&](uint32_t s) -> uint32_t {
-    return Mode == RING_BCAST ? a.epoch : a.epoch - ((s / kRingEntries) & 1u);
+    return Mode == RING_BCAST ? a.epoch : layout::ring_flag(a.epoch, s);
   };
   // A Broadcast has no packets coming back as credit: every tile has a
   // position of its own.

@@ -1224,6 +1224,8 @@ int ll_ring_shape(int nranks, int mode, uint64_t tiles, uint64_t area_bytes, uin
   return LL_OK;
 }
 
+uint32_t ll_ring_flag(uint32_t epoch, uint32_t step) { return L::ring_flag(epoch, step); }
+
 // A bounded-scratch AllReduce through the scratch region at scratch_base,
 // laid out for `layout_P` ranks (nranks <= layout_P: a call uses the first
 // nranks slices and the first nranks-1 slots of every area, whose offsets

@@ -99,6 +99,7 @@ _SIGS = {
     "ll_buffered_plan": (_i, [_sz, _i, _i, _sz, ctypes.POINTER(_u32), ctypes.POINTER(_sz)]),
     "ll_iteration_span": (_i, [_sz, _sz, _u32, _i, _i, ctypes.POINTER(ctypes.c_int64)]),
     "ll_ring_shape": (_i, [_i, _i, _u64, _u64, _u64, _u64, ctypes.POINTER(_u64)]),
+    "ll_ring_flag": (_u32, [_u32, _u32]),
     "ll_probe_empty": (_i, [_i, _i, _vp, _vp]),
     "ll_probe_floor": (_i, [_vp, _u64, _u64, _vp, _i, _i, _vp, _vp]),
     "ll_probe_chase": (_i, [_vp, _u64, _u64, _i, _vp, _vp]),
@@ -334,6 +335,10 @@ def ll_ring_shape(nranks: int, mode: int, tiles: int, area_bytes: int, per_wg: i
     out = (ctypes.c_uint64 * 4)()
     st = _lib.ll_ring_shape(nranks, mode, tiles, area_bytes, per_wg, max_wg, out)
     return st, tuple(out)
+
+
+def ll_ring_flag(epoch: int, step: int) -> int:
+    return _lib.ll_ring_flag(epoch, step)
 
 
 # ---------------------------------------------------------------- probes and benchmark loops

@@ -48,7 +48,7 @@ class Wave:
         self.rank, self.p, self.steps, self.epoch, self.s, self.published = rank, p, steps, epoch, 0, False
 
     def flag(self, s):
-        return self.epoch - (s // ENTRIES) % 2
+        return self.epoch if s // ENTRIES % 2 == 0 else 0
 
     def done(self):
         return self.s > self.steps
@@ -78,6 +78,44 @@ class Wave:
         return True
 
 
+def run_call(rng, ring, p, steps, epoch, wave=Wave):
+    """One call's waves (one a rank) on the ring, in a random order."""
+    waves = [wave(r, p, steps, epoch) for r in range(p)]
+    got = [set() for _ in range(p)]
+    bias = [rng.random() ** 3 + 1e-3 for _ in range(p)]  # some ranks run far more often than others
+    stuck = 0
+    while not all(w.done() for w in waves):
+        w = rng.choices(waves, bias)[0]
+        if w.done():
+            continue
+        stuck = 0 if w.advance(ring, got[w.rank]) else stuck + 1
+        assert stuck < 100_000, "the waves wait for each other"
+    assert all(len(g) == (p - 1) * steps for g in got)
+
+
+class LibraryWave(Wave):
+    """The same with the flag values of the library."""
+
+    def flag(self, s):
+        return ll.ll_ring_flag(self.epoch, s)
+
+
+@pytest.mark.parametrize("p", [2, 3])
+def test_a_call_runs_after_one_with_a_later_epoch(p):
+    """A call captured into a graph runs when the graph does, perhaps after
+    calls with later epochs: it must find none of its own flags in the ring,
+    whatever the steps of those calls, so a call writes no flag but its own
+    epoch and 0, which is no call's epoch."""
+    rng = random.Random(p)
+    for steps in (1, 4, 5, 8, 9, 13):
+        ring = [[[(0, -1)] * ENTRIES for _ in range(p)] for _ in range(p)]
+        run_call(rng, ring, p, steps, 8, LibraryWave)
+        assert {f for d in ring for s in d for f, _ in s} <= {0, 8}
+        run_call(rng, ring, p, 9, 7, LibraryWave)
+    for epoch in (1, 2, 0xFFFFFFFF):
+        assert [ll.ll_ring_flag(epoch, s) for s in range(13)] == [Wave(0, 2, 13, epoch).flag(s) for s in range(13)]
+
+
 @pytest.mark.parametrize("p", [2, 3, 8])
 def test_ring_protocol_under_any_schedule(p):
     """Whatever the order in which the ranks' waves run, every wave consumes
@@ -89,18 +127,7 @@ def test_ring_protocol_under_any_schedule(p):
         ring = [[[(0, -1)] * ENTRIES for _ in range(p)] for _ in range(p)]
         epoch = 1
         for call in range(4):
-            steps = rng.choice([0, 1, 2, 3, 4, 5, 8, 9, 13, 17])
-            waves = [Wave(r, p, steps, epoch) for r in range(p)]
-            got = [set() for _ in range(p)]
-            bias = [rng.random() ** 3 + 1e-3 for _ in range(p)]  # some ranks run far more often than others
-            stuck = 0
-            while not all(w.done() for w in waves):
-                w = rng.choices(waves, bias)[0]
-                if w.done():
-                    continue
-                stuck = 0 if w.advance(ring, got[w.rank]) else stuck + 1
-                assert stuck < 100_000, "the waves wait for each other"
-            assert all(len(g) == (p - 1) * steps for g in got)
+            run_call(rng, ring, p, rng.choice([0, 1, 2, 3, 4, 5, 8, 9, 13, 17]), epoch)
             epoch += rng.choice([1, 1, 2, 7])
 
 

@@ -238,3 +238,39 @@ def test_graph_replays(op, n):
         torch.cuda.synchronize()
         assert ll.ll_check(side.cuda_stream) == ll.LL_OK
         assert np.array_equal(reg.read_out(out_elems(op, p, n), NP[dtype]), want_of(op, x, 3)), f"{op} replay {rep}"
+
+
+@pytest.mark.parametrize("n,algo,ring_algo", [(16384, "auto", "auto"), (4096, "auto", "twoshot_waves"),
+                                              (16384, "oneshot_line", "twoshot_line")])
+def test_static_call_captured_before_a_ring_call_runs_after_it(n, algo, ring_algo):
+    """ll_allreduce_static takes its epoch when it is called: a captured call
+    is replayed after an eager call with a later epoch that went round the ring
+    more than once over the same positions.  The captured call must not take
+    any of that call's packets for its own."""
+    p, big = 8, 4 * MIB // 4
+    dev = lambda bits: torch.from_numpy(np.ascontiguousarray(bits).view(np.uint8).reshape(-1).copy()).cuda()  # noqa: E731
+    x, y = wl.normal(p, n, "f32", seed=5), wl.normal(p, big, "f32", seed=6)
+    xin, yin = dev(x), dev(y)
+    xout, yout = torch.zeros_like(xin), torch.zeros_like(yin)
+
+    def static(inp, out, m, name, s):
+        st, used = ll.ll_allreduce_static(inp.data_ptr(), out.data_ptr(), m, ll.LL_F32, ll.LL_SUM, p, s, ll.ALGOS[name])
+        assert st == ll.LL_OK, ll.ll_strerror(st)
+        return used
+
+    side = torch.cuda.Stream()
+    static(xin, xout, n, algo, side.cuda_stream)  # lazy set-up, before the capture
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=side):
+        assert static(xin, xout, n, algo, side.cuda_stream) == 1
+    torch.cuda.synchronize()
+    xout.zero_()
+    print(f"static {algo} n={n} captured, {ring_algo} in between", flush=True)
+    assert static(yin, yout, big, ring_algo, stream()) > 1
+    assert ll.ll_check(stream()) == ll.LL_OK
+    graph.replay()
+    torch.cuda.synchronize()
+    assert ll.ll_check(side.cuda_stream) == ll.LL_OK
+    assert np.array_equal(yout.cpu().numpy().view(np.uint32).reshape(p, big), oracle.allreduce(y))
+    assert np.array_equal(xout.cpu().numpy().view(np.uint32).reshape(p, n), oracle.allreduce(x))
