@@ -449,9 +449,20 @@ bool ring_size_ok(int mode, const Plan &pl, uint64_t total) {
 // 17.8 -> 16.8), except in the AllGather, which has no tiles to wait for.
 uint64_t ring_waves_per_cu(int mode, int P) { return P <= 3 && mode != RING_AG ? 16 : 8; }
 
-// Whether a ring kernel serves this call: no tuning field set, at most kRingMaxBytes per rank (32-bit stream offsets) and a size
-// for which it is the faster one.  Otherwise the call's other kernel runs.
-bool ring_serves(const Plan &pl, int *mode_out, uint64_t *total_out, uint64_t *chunk_out) {
+// How a call runs on a ring kernel.
+struct RingPlan {
+  int mode;
+  uint64_t total, chunk;
+  ring_fn fn;
+  L::RingShape sh;
+};
+
+// Whether a ring kernel serves this call: no tuning field set that it does not
+// have, at most kRingMaxBytes per rank (32-bit stream offsets), a size for which
+// it is the faster one, and a packet area that holds the ring of one workgroup.
+// Otherwise (*serves false) the call's other kernel runs.
+int ring_plan(const Plan &pl, RingPlan *rp, bool *serves) {
+  *serves = false;
   int mode;
   switch (pl.kind) {
     case K_TWOSHOT: case K_TWOSHOT_WAVES: mode = RING_AR; break;
@@ -459,40 +470,35 @@ bool ring_serves(const Plan &pl, int *mode_out, uint64_t *total_out, uint64_t *c
     case K_AG: case K_AG_WAVES: mode = RING_AG; break;
     case K_BCAST: mode = RING_BCAST; break;
     case K_REDUCE: mode = RING_REDUCE; break;
-    default: return false;
+    default: return LL_OK;
   }
   const CallOpts &o = pl.o;
   if (pl.proto == PR_SENT || o.forced_shape() || o.wave_units != 0 || o.wave_kernels != 0 || o.clear_slots != 0 ||
       o.lag != 1 || o.first_wait != 0 || o.poll_gap != 0 || o.phases != nullptr)
-    return false;
-  const int es = pl.dt == LL_BF16 ? 2 : 4;
+    return LL_OK;
+  const int P = pl.P, es = pl.dt == LL_BF16 ? 2 : 4;
   const bool blocks = mode == RING_RS || mode == RING_AG;  // P chunks of n elements
-  const uint64_t total = (uint64_t)pl.a.n * (uint64_t)es * (blocks ? (uint64_t)pl.P : 1);
-  if (total > L::kRingMaxBytes || !ring_size_ok(mode, pl, total)) return false;
-  *mode_out = mode;
-  *total_out = total;
-  *chunk_out = blocks ? total / (uint64_t)pl.P : L::twoshot_chunk((uint64_t)pl.a.n, pl.P, es) * (uint64_t)es;
-  return true;
-}
-
-// Launches the call on a ring kernel if one serves it: true, with the
-// call's status in *rc; false if the call must run another way.
-bool ring_launch(const Plan &pl, void *stream, int *rc) {
-  int mode;
-  uint64_t total, chunk;
-  if (!ring_serves(pl, &mode, &total, &chunk)) return false;
-  const int P = pl.P;
+  rp->mode = mode;
+  rp->total = (uint64_t)pl.a.n * (uint64_t)es * (blocks ? (uint64_t)P : 1);
+  if (rp->total > L::kRingMaxBytes || !ring_size_ok(mode, pl, rp->total)) return LL_OK;
+  rp->chunk = blocks ? rp->total / (uint64_t)P : L::twoshot_chunk((uint64_t)pl.a.n, P, es) * (uint64_t)es;
   const int odd = pl.a.al4 == 0 || (pl.a.in != nullptr && pl.a.in_al4 == 0) ? 1 : 0;  // bfloat16 only
-  const ring_fn fn = table().ring[mode][pl.proto == PR_LINE ? 1 : 0][pl.dt + odd][P];
+  rp->fn = table().ring[mode][pl.proto == PR_LINE ? 1 : 0][pl.dt + odd][P];
   int cap = 0;
+  int st = resident_grid(reinterpret_cast<const void *>(rp->fn), kRingThreads, &cap);
+  if (st != LL_OK) return st;
   DevInfo d;
-  if ((*rc = resident_grid(reinterpret_cast<const void *>(fn), kRingThreads, &cap)) != LL_OK) return true;
-  if ((*rc = device_info(&d)) != LL_OK) return true;
+  if ((st = device_info(&d)) != LL_OK) return st;
   constexpr uint64_t per_wg = kRingThreads / 64;
   const uint64_t max_wg = std::min((uint64_t)cap, ring_waves_per_cu(mode, P) * (uint64_t)d.cus / per_wg) / (uint64_t)P;
   const uint64_t tile = pl.proto == PR_LINE ? RingTile<ProtoLine>::kPayload : RingTile<ProtoLL>::kPayload;
-  L::RingShape sh;
-  if (!L::ring_shape(P, mode, L::ceil_div(chunk, tile), pl.area_bytes, per_wg, max_wg, &sh)) return false;
+  *serves = L::ring_shape(P, mode, L::ceil_div(rp->chunk, tile), pl.area_bytes, per_wg, max_wg, &rp->sh);
+  return LL_OK;
+}
+
+// Launches a call that a ring kernel serves (ring_plan).
+int ring_launch(const Plan &pl, const RingPlan &rp, void *stream) {
+  constexpr uint64_t per_wg = kRingThreads / 64;
   RingArgs a;
   memset(&a, 0, sizeof a);
   a.sym = pl.a.sym;
@@ -500,35 +506,39 @@ bool ring_launch(const Plan &pl, void *stream, int *rc) {
   a.in = pl.a.in != nullptr ? pl.a.in : pl.a.sym;  // by default inside the region, at offset 0 of every slice
   a.in_stride = pl.a.in != nullptr ? pl.a.in_stride : pl.a.stride;
   a.out = pl.a.out;
-  a.out_pitch = mode == RING_RS || mode == RING_REDUCE ? 0 : total;
+  a.out_pitch = rp.mode == RING_RS || rp.mode == RING_REDUCE ? 0 : rp.total;
   a.area = pl.a.area;
-  a.flags = pl.a.area + sh.flags;
+  a.flags = pl.a.area + rp.sh.flags;
   a.timeout = pl.o.timeout;
   a.stamps = pl.o.stamps;
-  a.total = (uint32_t)total;
-  a.chunk = (uint32_t)chunk;
-  a.slot = (uint32_t)sh.slot;
-  a.tiles = (uint32_t)sh.tiles;
-  a.waves = (uint32_t)sh.waves;
+  a.total = (uint32_t)rp.total;
+  a.chunk = (uint32_t)rp.chunk;
+  a.slot = (uint32_t)rp.sh.slot;
+  a.tiles = (uint32_t)rp.sh.tiles;
+  a.waves = (uint32_t)rp.sh.waves;
   a.epoch = pl.a.epoch;
   a.mute = pl.o.mute;
   a.root = (uint32_t)pl.a.root;
-  a.grid = (uint32_t)(sh.waves / per_wg * (uint64_t)P);
-  if ((*rc = status_of(stream, &a.status)) != LL_OK) return true;
-  hipLaunchKernelGGL(fn, dim3(a.grid), dim3(kRingThreads), 0, (hipStream_t)stream, a);
+  a.grid = (uint32_t)(rp.sh.waves / per_wg * (uint64_t)pl.P);
+  const int st = status_of(stream, &a.status);
+  if (st != LL_OK) return st;
+  hipLaunchKernelGGL(rp.fn, dim3(a.grid), dim3(kRingThreads), 0, (hipStream_t)stream, a);
   const hipError_t e = hipGetLastError();
   if (pl.o.grid_out) *pl.o.grid_out = (int)a.grid;
   if (pl.o.threads_out) *pl.o.threads_out = kRingThreads;
   if (e != hipSuccess) {
     t_last_hip = (int)e;
-    *rc = LL_ERR_HIP;
+    return LL_ERR_HIP;
   }
-  return true;
+  return LL_OK;
 }
 
 int launch(const Plan &pl, void *stream) {
-  int ring_rc = LL_OK;
-  if (ring_launch(pl, stream, &ring_rc)) return ring_rc;
+  RingPlan rp;
+  bool ring = false;
+  const int ring_st = ring_plan(pl, &rp, &ring);
+  if (ring_st != LL_OK) return ring_st;
+  if (ring) return ring_launch(pl, rp, stream);
   const bool two_waves = pl.kind == K_TWOSHOT_WAVES || pl.kind == K_RS_WAVES || pl.kind == K_AG_WAVES;
   const bool wave_kernel = pl.kind == K_ONESHOT_WAVES || two_waves;
   const int wpr = pl.proto == PR_SENT ? 1 : (pl.proto == PR_LINE ? 2 : 0);
@@ -1268,43 +1278,53 @@ static int buffered_call(const void *in, void *out, size_t count, ll_dtype dt, l
   uint64_t iter_count = 0, iters = 0;
   buffered_iterations(count, es, D, &iter_count, &iters);
   if ((uint64_t)epoch + iters - 1 > 0xFFFFFFFFull) return LL_ERR_INVALID;
+  // The call's plan with a named algorithm.
+  const uint64_t a8 = L::area8(D, layout_P), a128 = L::area128(D, layout_P), as = L::areaS(D, layout_P);
+  auto plan_with = [&](ll_algo named) {
+    Plan pl;
+    pl.dt = (int)dt;
+    pl.P = nranks;
+    pl.o = o;
+    pl.a = base_args(scratch_base, scratch_stride, out, epoch);
+    pl.a.in = (const char *)in;
+    pl.a.in_stride = in_bytes;
+    pl.a.in_al4 = (in_bytes % 4 == 0) ? 1u : 0u;
+    pl.a.n = (int64_t)count;
+    pl.a.al4 = (in_bytes % 4 == 0) ? 1u : 0u;
+    pl.a.iters = (uint32_t)iters;
+    pl.a.iter_n = (int64_t)iter_count;
+    plan_allreduce(&pl, named, count, es, nranks, iter_count, [&](int proto) {
+      return proto == PR_LINE ? 2 * a8 : (proto == PR_SENT ? 2 * (a8 + a128) : (uint64_t)0);
+    });
+    pl.a.sub_bytes = pl.proto == PR_LINE ? a128 : (pl.proto == PR_SENT ? as : a8);
+    pl.area_bytes = 2 * pl.a.sub_bytes;
+    return pl;
+  };
+  if (algo == LL_ALGO_AUTO && iters > 1) {
+    // several iterations: a ring kernel where one serves the call, with lines
+    // unless the call forbids them
+    const Plan pl = plan_with(o.lines_ok() ? LL_ALGO_TWOSHOT_LINE_WAVES : LL_ALGO_TWOSHOT_WAVES);
+    RingPlan rp;
+    bool ring = false;
+    st = ring_plan(pl, &rp, &ring);
+    if (st == LL_OK && ring) {
+      st = ring_launch(pl, rp, stream);
+      if (st == LL_OK && epochs_used != nullptr) *epochs_used = (uint32_t)iters;
+    }
+    if (st != LL_OK || ring) return st;
+  }
   if (algo == LL_ALGO_AUTO) {
-    // by the iteration size; the one-shot wave kernels run one iteration
-    // only, and the two-shot wave kernels take their place (measured on the
-    // paper's scratch study shape, 32 MiB at 8 ranks in 256 KiB .. 32 MiB
-    // iterations)
+    // otherwise by the iteration size; the one-shot wave kernels run one
+    // iteration only, and the two-shot wave kernels take their place
     // (every scratch region holds all three formats)
     algo = auto_choice(iter_count * es, nranks, auto_formats(L::kFmt8 | L::kFmtLine | L::kFmtSent, o));
     if (iters > 1 && algo == LL_ALGO_ONESHOT_WAVES) algo = LL_ALGO_TWOSHOT_WAVES;
     if (iters > 1 && algo == LL_ALGO_ONESHOT_SENTINEL_WAVES) algo = LL_ALGO_TWOSHOT_SENTINEL_WAVES;
     if (iters > 1 && algo == LL_ALGO_ONESHOT_LINE_WAVES) algo = LL_ALGO_TWOSHOT_LINE_WAVES;
-    // several iterations: the ring kernels (ring_serves), with
-    // lines unless the call forbids them
-    if (iters > 1 && in_bytes <= L::kRingMaxBytes)
-      algo = o.lines_ok() ? LL_ALGO_TWOSHOT_LINE_WAVES : LL_ALGO_TWOSHOT_WAVES;
   }
   if (iters > 1 && is_wave_algo(algo))
     return LL_ERR_UNSUPPORTED;
-
-  Plan pl;
-  pl.dt = (int)dt;
-  pl.P = nranks;
-  pl.o = o;
-  pl.a = base_args(scratch_base, scratch_stride, out, epoch);
-  pl.a.in = (const char *)in;
-  pl.a.in_stride = in_bytes;
-  pl.a.in_al4 = (in_bytes % 4 == 0) ? 1u : 0u;
-  pl.a.n = (int64_t)count;
-  pl.a.al4 = (in_bytes % 4 == 0) ? 1u : 0u;
-  pl.a.iters = (uint32_t)iters;
-  pl.a.iter_n = (int64_t)iter_count;
-  const uint64_t a8 = L::area8(D, layout_P), a128 = L::area128(D, layout_P), as = L::areaS(D, layout_P);
-  plan_allreduce(&pl, algo, count, es, nranks, iter_count, [&](int proto) {
-    return proto == PR_LINE ? 2 * a8 : (proto == PR_SENT ? 2 * (a8 + a128) : (uint64_t)0);
-  });
-  pl.a.sub_bytes = pl.proto == PR_LINE ? a128 : (pl.proto == PR_SENT ? as : a8);
-  pl.area_bytes = 2 * pl.a.sub_bytes;
-  st = launch(pl, stream);
+  st = launch(plan_with(algo), stream);
   if (st == LL_OK && epochs_used != nullptr) *epochs_used = (uint32_t)iters;
   return st;
 }

@@ -274,3 +274,32 @@ def test_static_call_captured_before_a_ring_call_runs_after_it(n, algo, ring_alg
     assert ll.ll_check(side.cuda_stream) == ll.LL_OK
     assert np.array_equal(yout.cpu().numpy().view(np.uint32).reshape(p, big), oracle.allreduce(y))
     assert np.array_equal(xout.cpu().numpy().view(np.uint32).reshape(p, n), oracle.allreduce(x))
+
+
+@pytest.mark.parametrize("iter_bytes,sentinel,tuning,named", [
+    (8192, False, {"pipeline_lag": 2}, "twoshot_waves"),            # a call the ring kernels do not serve
+    (65536, True, {"pipeline_lag": 2}, "twoshot_sentinel_waves"),
+    (1024, False, {}, "twoshot_waves"),                             # a scratch too small for a workgroup's ring
+    (1024, True, {}, "twoshot_waves"),
+    (8192, False, {}, "twoshot_line_waves"),                        # on the ring
+    (65536, True, {}, "twoshot_line_waves")])
+def test_bounded_scratch_auto_takes_the_ring_only_where_it_runs(iter_bytes, sentinel, tuning, named):
+    """AUTO in several iterations: the ring kernel's format where it serves the
+    call, and otherwise the algorithm measured for the iteration's size.  The
+    scratch holds the same bytes after the call as after the named algorithm's."""
+    p, dtype = 8, "bf16"
+    n = 5 * iter_bytes // 2 + 6
+    images = {}
+    for algo in ("auto", named):
+        reg = ScratchRegion(p, n, dtype, iter_bytes=iter_bytes)
+        reg.init()
+        x = wl.normal(p, n, dtype, seed=12)
+        reg.write_inputs(x)
+        flags = ll.LL_OPT_AUTO_SENTINEL if sentinel else 0
+        print(f"{algo} {iter_bytes} sentinel={sentinel} {tuning}", flush=True)
+        assert reg.allreduce(n, algo, opt=opts(flags=flags, **tuning)) == ll.LL_OK
+        assert ll.ll_check(stream()) == ll.LL_OK
+        assert reg.last_iters > 1
+        assert np.array_equal(reg.read_out(p * n, NP[dtype]).reshape(p, n), oracle.allreduce(x)), algo
+        images[algo] = reg.scratch.cpu().numpy().copy()
+    assert np.array_equal(images["auto"], images[named])
