@@ -424,15 +424,13 @@ int launch_tile(tile_fn fn, const Plan &pl, int W, void *stream);
 // A bounded-scratch call of several iterations always does: it would pay two
 // exchanges per iteration (32 MiB at 8 ranks in 1 MiB iterations 345 -> 161
 // us, in 256 KiB iterations 540 -> 219 us).
-constexpr uint64_t kRingAllGatherBytes = 256u << 10;
-
 bool ring_size_ok(int mode, const Plan &pl, uint64_t total) {
   const uint64_t KiB = 1024, MiB = 1024 * 1024;
   const int P = pl.P;
   switch (mode) {
     case RING_AR: return pl.a.iters > 1 || total * P >= (pl.proto == PR_LINE ? 7 : 5) * MiB;
     case RING_RS: return total * P >= 32 * MiB;
-    case RING_AG: return total >= kRingAllGatherBytes;
+    case RING_AG: return total >= 256 * KiB;
     case RING_BCAST: return total >= (P == 8 ? 128 * KiB : (P >= 4 ? 1 * MiB : 4 * MiB));
     default: return total >= (P == 8 ? 128 * KiB : (P >= 4 ? 2 * MiB : 16 * MiB));
   }
@@ -1490,30 +1488,42 @@ int ll_allgather_ex(void *sym_base, size_t rank_stride, void *out, size_t sendco
   Region rg;
   st = region_of(rank_stride, nranks, in_bytes, &rg);
   if (st != LL_OK) return st;
+  // The call's plan in a named format.
+  auto plan_with = [&](ll_proto named) {
+    Plan pl;
+    pl.kind = use_wave_kernel(named, in_bytes * nranks, nranks, true, o) ? K_AG_WAVES : K_AG;
+    pl.dt = (int)dt;
+    pl.P = nranks;
+    pl.o = o;
+    pl.proto = named == LL_PROTO_LINE128 ? PR_LINE : (named == LL_PROTO_SENTINEL ? PR_SENT : PR_LL);
+    pl.a = base_args(sym_base, rank_stride, out, epoch);
+    pl.a.n = (int64_t)sendcount;
+    pl.a.al4 = (in_bytes % 4 == 0) ? 1u : 0u;
+    pl.a.area = rg.area_of(pl.proto);
+    pl.area_bytes = rg.area_bytes(pl.proto);
+    pl.a.slot = slot_bytes(pl.proto, in_bytes);
+    pl.units = units_of(pl.proto, in_bytes);
+    return pl;
+  };
   if (proto == LL_PROTO_AUTO) {
-    // from the size where the ring AllGather runs, its packets carry no data
-    // and no format is faster than lines (8 ranks, 128 KiB per rank sent: 4.7
-    // us, sentinel units 6.4)
-    const bool ring = in_bytes * nranks >= kRingAllGatherBytes;
-    proto = proto_choice(auto_proto(in_bytes * nranks, nranks, o.sentinel_ok() && !ring, true), auto_formats(rg.fmt, o));
+    const unsigned allowed = auto_formats(rg.fmt, o);
+    proto = proto_choice(auto_proto(in_bytes * nranks, nranks, o.sentinel_ok(), true), allowed);
     if (proto == LL_PROTO_AUTO) return LL_ERR_SCRATCH;
+    const unsigned flagged = allowed & (L::kFmt8 | L::kFmtLine);
+    if (proto == LL_PROTO_SENTINEL && flagged != 0 && sendcount != 0) {
+      // sentinel units are slower than a ring kernel, whose packets carry no
+      // data (8 ranks, 128 KiB per rank sent: 6.4 us against 4.7), and have none
+      const ll_proto named = proto_choice(LL_PROTO_LINE128, flagged);
+      const Plan pl = plan_with(named);
+      RingPlan rp;
+      bool ring = false;
+      if ((st = ring_plan(pl, &rp, &ring)) != LL_OK) return st;
+      if (ring) return ring_launch(pl, rp, stream);
+    }
   }
   if ((rg.fmt & proto_fmt(proto)) == 0) return LL_ERR_SCRATCH;
   if (sendcount == 0) return LL_OK;
-  Plan pl;
-  pl.kind = use_wave_kernel(proto, in_bytes * nranks, nranks, true, o) ? K_AG_WAVES : K_AG;
-  pl.dt = (int)dt;
-  pl.P = nranks;
-  pl.o = o;
-  pl.proto = proto == LL_PROTO_LINE128 ? PR_LINE : (proto == LL_PROTO_SENTINEL ? PR_SENT : PR_LL);
-  pl.a = base_args(sym_base, rank_stride, out, epoch);
-  pl.a.n = (int64_t)sendcount;
-  pl.a.al4 = (in_bytes % 4 == 0) ? 1u : 0u;
-  pl.a.area = rg.area_of(pl.proto);
-  pl.area_bytes = rg.area_bytes(pl.proto);
-  pl.a.slot = slot_bytes(pl.proto, in_bytes);
-  pl.units = units_of(pl.proto, in_bytes);
-  return launch(pl, stream);
+  return launch(plan_with(proto), stream);
 }
 
 int ll_allgather(void *sym_base, size_t rank_stride, void *out, size_t sendcount, ll_dtype dt, int nranks,

@@ -303,3 +303,19 @@ def test_bounded_scratch_auto_takes_the_ring_only_where_it_runs(iter_bytes, sent
         assert np.array_equal(reg.read_out(p * n, NP[dtype]).reshape(p, n), oracle.allreduce(x)), algo
         images[algo] = reg.scratch.cpu().numpy().copy()
     assert np.array_equal(images["auto"], images[named])
+
+
+@pytest.mark.parametrize("tuning,proto,ring", [({}, "line128", True), ({"clear_slots": 2}, "sentinel", False)])
+def test_allgather_with_sentinel_units_allowed(tuning, proto, ring):
+    """AUTO with sentinel units allowed, from the ring AllGather's size on: the
+    ring kernel where it serves the call, otherwise sentinel units.  The
+    region holds the same bytes after the call as after the named format's."""
+    p, n, dtype = 8, 64 * KIB, "bf16"
+    images = []
+    for name, flags in (("auto", ll.LL_OPT_AUTO_SENTINEL), (proto, 0)):
+        reg = SymRegion(p, n, dtype)
+        reg.sym.zero_()
+        reg.init()
+        check(reg, "allgather", n, p, dtype, 0, ring, f"allgather {name} {tuning}", opts(flags=flags, **tuning), proto=name)
+        images.append(reg.sym.cpu().numpy().copy())
+    assert np.array_equal(*images)
