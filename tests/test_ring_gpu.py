@@ -17,6 +17,7 @@ from paper_2607_16100_amd import workloads as wl  # noqa: E402
 if torch.cuda.is_available():
     from paper_2607_16100_amd import llcoll as ll  # noqa: E402
     from paper_2607_16100_amd.region import ScratchRegion, SymRegion  # noqa: E402
+    from test_edge_gpu import assert_same, edge_inputs  # noqa: E402
 else:  # pragma: no cover
     pytest.skip("no GPU", allow_module_level=True)
 
@@ -58,16 +59,53 @@ def check(reg, op, n, p, dtype, root, ring, what, opt=None, **kw):
     reg.write_inputs(x)
     reg.out.fill_(0xA5)
     opt = opt or opts()
+    if p == 2:  # its wave-per-peer kernels have workgroups of the ring's size: read the region
+        reg.init()
     assert call(reg, op, n, p, root, opt, **kw) == ll.LL_OK, what
     assert ll.ll_check(stream()) == ll.LL_OK, what
-    if p != 2:  # at 2 ranks the wave-per-peer kernels have workgroups of the same size
+    if p != 2:
         assert (opt.threads == RING_THREADS) == ring, f"{what}: on a workgroup of {opt.threads} threads"
+    else:
+        packet8 = kw.get("proto") == "packet8" or kw.get("algo") == "twoshot_waves"
+        st, offs = ll.ll_slice_layout(reg.rank_stride, p)
+        area = reg.sym.view(p, -1)[:, offs[1 if packet8 else 2]:offs[2 if packet8 else 3]]
+        assert went_round_the_ring(area, op, n, dtype, packet8, reg.epoch, root) == ring, what
     total = out_elems(op, p, n)
     got = reg.read_out(total, NP[dtype])
     bad = np.flatnonzero(got != want_of(op, x, root))
     assert bad.size == 0, f"{what}: {bad.size} elements differ, first at {bad[0]}"
     if total * ES[dtype] < reg.out.numel():
         assert (reg.out[total * ES[dtype]:total * ES[dtype] + 4096] == 0xA5).all(), f"{what}: wrote past the outputs"
+
+
+def went_round_the_ring(area, op, n, dtype, packet8, epoch, root=0):
+    """Whether a 2-rank call whose packet area was clear before it ran on a ring
+    kernel, from what it left there: on the ring every wave's completion block
+    holds the epoch and nothing else (another kernel leaves the area clear there,
+    or payload); a ReduceScatter has none, and leaves the area clear behind the
+    ring, where another kernel's slot still has packets."""
+    p, mode, es = 2, list(FIRST).index(op), ES[dtype]
+    chunk = {"reduce_scatter": n // p * es, "allgather": n * es}.get(op, -(-(-(-n // p)) // (16 // es)) * 16)
+    tiles = -(-chunk // (512 if packet8 else 960))
+    waves_per_cu = 8 if op == "allgather" else 16
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    st, (_, waves, slot, flags) = ll.ll_ring_shape(p, mode, tiles, area.shape[1], 2, waves_per_cu * cus // 2 // p)
+    assert st == ll.LL_OK
+    if op == "reduce_scatter":
+        assert slot < tiles * 1024  # or the other kernel's slot would end inside the ring's
+        return not bool(area[:, slot:tiles * 1024].any())
+    blocks = area[:, flags:flags + waves * 64].cpu().numpy().view(np.uint32).reshape(p, waves, 16)
+    if op == "reduce":  # only the root is told
+        blocks = blocks[root:root + 1]
+    return bool((blocks[..., 15] == epoch).all() and not blocks[..., :15].any())
+
+
+def scratch_area(d, packet8):
+    """Byte range of the flagged sub-buffers in a 2-rank scratch slice for iterations of d bytes."""
+    chunk = (-(-d // 2) + 4 + 15) // 16 * 16
+    a8, a128 = (max(f(d), 2 * f(chunk)) for f in (lambda b: -(-(-(-b // 4) * 8) // 256) * 256,
+                                                  lambda b: -(-(-(-b // 4)) // 240) * 1024))
+    return (0, 2 * a8) if packet8 else (2 * a8, 2 * a8 + 2 * a128)
 
 
 # (operation, first size per rank in bytes on the ring, by rank count)
@@ -103,6 +141,8 @@ def test_sizes_at_the_edges(op, p, dtype):
         for i, n in enumerate(sizes):
             ring = i > 0
             check(reg, op, n, p, dtype, root, ring if n >= first else False, f"{op} P={p} {dtype} n={n} root={root}")
+        # the same size with a tuning field set, which the ring kernels leave to the others
+        check(reg, op, first, p, dtype, root, False, f"{op} P={p} {dtype} n={first} root={root} tuned", opts(pipeline_lag=2))
 
 
 @pytest.mark.parametrize("op", list(FIRST))
@@ -183,11 +223,38 @@ def test_bounded_scratch_goes_round_the_ring(p, dtype, iter_bytes, in_place):
         x = wl.normal(p, n, dtype, seed=10 * k + p)
         reg.write_inputs(x)
         opt = opts()
+        if p == 2:  # as in check()
+            reg.init()
         print(f"P={p} {dtype} {iter_bytes} in_place={in_place} {algo}", flush=True)
         assert reg.allreduce(n, algo, opt=opt) == ll.LL_OK
         assert ll.ll_check(stream()) == ll.LL_OK
         assert opt.threads == RING_THREADS and reg.last_iters > 1
+        if p == 2:
+            packet8 = algo == "twoshot_waves"
+            lo, hi = scratch_area(reg.iter_bytes, packet8)
+            assert went_round_the_ring(reg.scratch.view(p, -1)[:, lo:hi], "allreduce", n, dtype, packet8,
+                                       reg.epoch - reg.last_iters + 1)
         assert np.array_equal(reg.read_out(p * n, NP[dtype]).reshape(p, n), oracle.allreduce(x)), algo
+
+
+@pytest.mark.parametrize("op", ["allreduce", "reduce_scatter", "reduce"])
+@pytest.mark.parametrize("p,dtype", [(3, "f32"), (8, "f32"), (8, "bf16")])
+def test_infinities_nan_and_overflow(op, p, dtype):
+    """The edges of IEEE arithmetic and of the rounding to bfloat16 (the columns
+    of test_edge_gpu.py, repeated over the whole message) on the ring kernels."""
+    es = ES[dtype]
+    n = -(-FIRST[op](p) // es // (2 * p)) * 2 * p + 2 * p
+    cols = edge_inputs(p, dtype, repeat=1)
+    x = np.ascontiguousarray(np.tile(cols, (1, -(-n // cols.shape[1])))[:, :n])
+    reg = SymRegion(p, n, dtype, out_elems=out_elems(op, p, n))
+    reg.init()
+    reg.write_inputs(x)
+    opt = opts()
+    print(op, p, dtype, n, flush=True)
+    assert call(reg, op, n, p, 1, opt) == ll.LL_OK
+    assert ll.ll_check(stream()) == ll.LL_OK
+    assert opt.threads == RING_THREADS
+    assert_same(reg.read_out(out_elems(op, p, n), NP[dtype]), want_of(op, x, 1), f"{op} P={p} {dtype}")
 
 
 @pytest.mark.parametrize("op", list(FIRST))
