@@ -1,6 +1,7 @@
 """Benchmark of the barrier-free collectives on one MI355X.
 
-Headline (one JSON line on stdout):
+Headline (one JSON line on stdout; the results of every section go to stderr,
+where the last line, "all sections: {...}", holds them all):
   * p50 microseconds per AllReduce at 16 KiB per rank: 8 virtual ranks,
     bfloat16, batch 1 x hidden 8192, normal(0,1) inputs, the library's
     default algorithm for that size (one-shot, 8-byte packets), `--steps`
@@ -748,6 +749,80 @@ def traffic_from_profiles(kernel_hash: str, grid_threads: int):
     return d.get("hbm_bytes_per_launch")
 
 
+def result_line(result, steps, warmup):
+    """The JSON line of a run: the headline, its bounds and the CPU baseline.  The
+    sections' own results stay out of it (main logs them): with all of them the
+    line grew past 16 KB, more than a record of the run's last output holds."""
+    h = result.get("headline", {})
+    fl = result.get("floor", {}).get("floor", {})
+    c3 = result.get("c3")
+    bw = result.get("bw", {}).get(BW_ALGO)
+    khash = kernel_source_hash()
+    roofline = None
+    if bw:
+        roofline = {"bound": "hbm", "achieved": round(bw["gbps"], 1), "peak": PEAK_HBM_GBS, "unit": "GB/s",
+                    "frac": round(bw["gbps"] / PEAK_HBM_GBS, 4),
+                    "traffic": traffic_from_profiles(khash, bw["grid"] * bw["threads"]),
+                    "kernel": BW_KERNEL,
+                    "kernel_us": round(bw["kernel_us"], 2), "algorithmic_bytes": bw["algorithmic_bytes"]}
+        if roofline["traffic"]:
+            # the counters' bytes (FETCH_SIZE + WRITE_SIZE, calibrated) over the same kernel time
+            roofline["traffic_gbps"] = round(roofline["traffic"] / bw["kernel_us"] / 1e3, 1)
+        probe = result.get("copy", {}).get("streaming_probe", {}).get("copy")
+        if probe:
+            # the best plain streaming copy on the same GPU: what a simple kernel reaches
+            roofline["copy_ceiling_gbps"] = round(probe["gbps"], 1)
+            roofline["frac_of_copy_ceiling"] = round(bw["gbps"] / probe["gbps"], 4)
+    if h and fl:
+        ex = h.get("exchange_probe", {})
+        lat = {"bound": "latency floor: back-to-back launches of a kernel with the same grid doing one dependent "
+                        "HBM load (empty-kernel launch + one HBM round trip)",
+               "kernel": "k_oneshot_tile<ProtoLL, bf16, 8> (16 KiB per rank, 8 ranks, one tile per workgroup)",
+               "p50_us": round(h["p50_us"], 3), "floor_p50_us": round(fl["p50_us"], 3),
+               "ratio_to_floor": round(h["p50_us"] / fl["p50_us"], 3), "target_ratio": 1.5,
+               "composed_floor_us": round(result["floor"].get("composed_p50_us", float("nan")), 3),
+               "kernel_span_p50_us": round(h["span_p50_us"], 3),
+               "floor_span_p50_us": round(fl["span_p50_us"], 3),
+               "stamp_free_mean_us": round(h["stamp_free_mean_us"], 3),
+               "floor_stamp_free_mean_us": round(fl["stamp_free_mean_us"], 3),
+               "ratio_to_floor_stamp_free": round(h["stamp_free_mean_us"] / fl["stamp_free_mean_us"], 3)}
+        if ex:
+            lat.update({"exchange_probe_p50_us": round(ex["p50_us"], 3),
+                        "exchange_probe_stamp_free_mean_us": round(ex["stamp_free_mean_us"], 3),
+                        "ratio_to_exchange_probe": round(h["p50_us"] / ex["p50_us"], 3)})
+        if roofline is None:
+            roofline = {"bound": "latency", "achieved": lat["p50_us"], "peak": lat["floor_p50_us"], "unit": "us",
+                        "frac": round(lat["floor_p50_us"] / lat["p50_us"], 4), "traffic": None}
+        roofline["latency"] = lat
+    return {
+        "metric": "p50 µs per AllReduce at 16 KB (P=8, bf16) + HBM GB/s at 64 MB",
+        "value": round(h["p50_us"], 3) if h else None,
+        "unit": "µs",
+        "n_gpus": 1,
+        "steps": steps,
+        "warmup": warmup,
+        "ms_per_step": round(h["mean_us"] / 1000.0, 6) if h else None,
+        "higher_is_better": False,
+        "scaling": "weak",
+        "vs_baseline": None,
+        "dtype": "f32",
+        "data": "synthetic",
+        "config": {"workload": "AllReduce sum, 8 virtual ranks on one GPU, bf16 batch 1 x hidden 8192 "
+                               "(16 KiB per rank), one-shot 8-byte packets (one wave per peer), back-to-back calls",
+                   "ranks": 8, "elements_per_rank": 8192, "element_type": "bf16", "accumulate": "f32",
+                   "parallelism": "8 virtual ranks / 1 GPU"},
+        "p99_us": round(h["p99_us"], 3) if h else None,
+        "floor_p50_us": round(fl["p50_us"], 3) if fl else None,
+        "ratio_to_floor": round(h["p50_us"] / fl["p50_us"], 3) if (h and fl) else None,
+        "hbm_gbps_64MB": round(bw["gbps"], 1) if bw else None,
+        "c3_1MiB": ({k: {"p50_us": round(c3[k]["p50_us"], 3), "frac_of_bound": c3[k]["frac_of_bound"]}
+                     for k in ("auto", "auto_sentinel_allowed")} | {"bound_us": c3["auto"]["bound_us"]}) if c3 else None,
+        "roofline": roofline,
+        "cpu_baseline": result.get("cpu"),
+        "kernel_source_hash": khash,
+    }
+
+
 def main():
     ap = argparse.ArgumentParser()
     ap.add_argument("--gpus", type=int, default=1)
@@ -828,76 +903,8 @@ def main():
         result["cpu"] = bench_cpu_baseline(args.cpu_seconds)
         log(json.dumps(result["cpu"]))
 
-    h = result.get("headline", {})
-    fl = result.get("floor", {}).get("floor", {})
-    c3 = result.get("c3")
-    bw = result.get("bw", {}).get(BW_ALGO)
-    khash = kernel_source_hash()
-    roofline = None
-    if bw:
-        roofline = {"bound": "hbm", "achieved": round(bw["gbps"], 1), "peak": PEAK_HBM_GBS, "unit": "GB/s",
-                    "frac": round(bw["gbps"] / PEAK_HBM_GBS, 4),
-                    "traffic": traffic_from_profiles(khash, bw["grid"] * bw["threads"]),
-                    "kernel": BW_KERNEL,
-                    "kernel_us": round(bw["kernel_us"], 2), "algorithmic_bytes": bw["algorithmic_bytes"]}
-        if roofline["traffic"]:
-            # the counters' bytes (FETCH_SIZE + WRITE_SIZE, calibrated) over the same kernel time
-            roofline["traffic_gbps"] = round(roofline["traffic"] / bw["kernel_us"] / 1e3, 1)
-        probe = result.get("copy", {}).get("streaming_probe", {}).get("copy")
-        if probe:
-            # the best plain streaming copy on the same GPU: what a simple kernel reaches
-            roofline["copy_ceiling_gbps"] = round(probe["gbps"], 1)
-            roofline["frac_of_copy_ceiling"] = round(bw["gbps"] / probe["gbps"], 4)
-    if h and fl:
-        ex = h.get("exchange_probe", {})
-        lat = {"bound": "latency floor: back-to-back launches of a kernel with the same grid doing one dependent "
-                        "HBM load (empty-kernel launch + one HBM round trip)",
-               "kernel": "k_oneshot_tile<ProtoLL, bf16, 8> (16 KiB per rank, 8 ranks, one tile per workgroup)",
-               "p50_us": round(h["p50_us"], 3), "floor_p50_us": round(fl["p50_us"], 3),
-               "ratio_to_floor": round(h["p50_us"] / fl["p50_us"], 3), "target_ratio": 1.5,
-               "composed_floor_us": round(result["floor"].get("composed_p50_us", float("nan")), 3),
-               "kernel_span_p50_us": round(h["span_p50_us"], 3),
-               "floor_span_p50_us": round(fl["span_p50_us"], 3),
-               "stamp_free_mean_us": round(h["stamp_free_mean_us"], 3),
-               "floor_stamp_free_mean_us": round(fl["stamp_free_mean_us"], 3),
-               "ratio_to_floor_stamp_free": round(h["stamp_free_mean_us"] / fl["stamp_free_mean_us"], 3)}
-        if ex:
-            lat.update({"exchange_probe_p50_us": round(ex["p50_us"], 3),
-                        "exchange_probe_stamp_free_mean_us": round(ex["stamp_free_mean_us"], 3),
-                        "ratio_to_exchange_probe": round(h["p50_us"] / ex["p50_us"], 3)})
-        if roofline is None:
-            roofline = {"bound": "latency", "achieved": lat["p50_us"], "peak": lat["floor_p50_us"], "unit": "us",
-                        "frac": round(lat["floor_p50_us"] / lat["p50_us"], 4), "traffic": None}
-        roofline["latency"] = lat
-    line = {
-        "metric": "p50 µs per AllReduce at 16 KB (P=8, bf16) + HBM GB/s at 64 MB",
-        "value": round(h["p50_us"], 3) if h else None,
-        "unit": "µs",
-        "n_gpus": 1,
-        "steps": args.steps,
-        "warmup": args.warmup,
-        "ms_per_step": round(h["mean_us"] / 1000.0, 6) if h else None,
-        "higher_is_better": False,
-        "scaling": "weak",
-        "vs_baseline": None,
-        "dtype": "f32",
-        "data": "synthetic",
-        "config": {"workload": "AllReduce sum, 8 virtual ranks on one GPU, bf16 batch 1 x hidden 8192 "
-                               "(16 KiB per rank), one-shot 8-byte packets (one wave per peer), back-to-back calls",
-                   "ranks": 8, "elements_per_rank": 8192, "element_type": "bf16", "accumulate": "f32",
-                   "parallelism": "8 virtual ranks / 1 GPU"},
-        "p99_us": round(h["p99_us"], 3) if h else None,
-        "floor_p50_us": round(fl["p50_us"], 3) if fl else None,
-        "ratio_to_floor": round(h["p50_us"] / fl["p50_us"], 3) if (h and fl) else None,
-        "hbm_gbps_64MB": round(bw["gbps"], 1) if bw else None,
-        "c3_1MiB": ({k: {"p50_us": round(c3[k]["p50_us"], 3), "frac_of_bound": c3[k]["frac_of_bound"]}
-                     for k in ("auto", "auto_sentinel_allowed")} | {"bound_us": c3["auto"]["bound_us"]}) if c3 else None,
-        "roofline": roofline,
-        "cpu_baseline": result.get("cpu"),
-        "detail": result,
-        "kernel_source_hash": khash,
-    }
-    print(json.dumps(line), flush=True)
+    log("all sections: " + json.dumps(result))
+    print(json.dumps(result_line(result, args.steps, args.warmup)), flush=True)
 
 
 if __name__ == "__main__":
