@@ -552,7 +552,7 @@ def bench_sol_pieces(torch, ll):
     }
 
 
-RING_MIN_BYTES = {"line128": 7 << 20, "packet8": 5 << 20}  # all ranks' inputs from which a two-shot runs on the ring
+RING_MIN_BYTES = {"line128": 7680 << 10, "packet8": 5 << 20}  # all ranks' inputs from which a two-shot runs on the ring (8 ranks)
 
 
 def moved_bytes(algo, p, count, esize):

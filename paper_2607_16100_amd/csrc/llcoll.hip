@@ -397,43 +397,77 @@ int launch_kernel(kernel_fn fn, const Plan &pl, int W, int threads, void *stream
 int launch_tile(tile_fn fn, const Plan &pl, int W, void *stream);
 
 // ---------------------------------------------------------------- ring kernels
-// Total bytes (all ranks' inputs; AllGather: one rank's output) from which a
-// call runs on a ring kernel (ll_ring.hpp), measured on MI355X at every rank
-// count against the kernel that served the call before, bfloat16, p50 of
-// back-to-back calls:
-//  - AllReduce, lines: 7 MiB over the ranks.  8 ranks: 768 KiB per rank 8.50
-//    us against 8.28 us, 1 MiB 9.20 against 10.62, 4 MiB 21.9 against 30.9,
-//    64 MiB 308 against 500; 4 ranks: 1 MiB 7.27 against 6.34, 2 MiB 8.95
-//    against 9.67; 2 ranks: 3 MiB 7.08 against 6.44, 4 MiB 7.32 against 7.52.
-//  - AllReduce, 8-byte packets: 5 MiB (8 ranks: 512 KiB per rank 8.77 against
-//    8.48, 1 MiB 13.8 against 15.2; 4 ranks: 1 MiB 7.82 against 8.28).
-//  - ReduceScatter: 32 MiB (8 ranks: 2 MiB per rank 12.6 against 9.7, 4 MiB
-//    17.5 against 17.8, 8 MiB 33.2 against 36.3; 4 ranks: 4 MiB 10.3 against
-//    9.3, 8 MiB 16.8 against 19.1).
-//  - AllGather: 256 KiB of output per rank, up to which the one-tile kernel
-//    serves (8 ranks: 224 KiB 3.22 us against 3.25, 256 KiB 3.11 against 3.84, 2
-//    MiB 6.26 against 11.8, 16 MiB 26.4 against 67.4; 4 ranks: 128 KiB 2.98
-//    against 2.82, 256 KiB 2.99 against 3.19).
-//  - Broadcast, Reduce (bytes per rank): at 8 ranks, a rank per XCD, 128 KiB
-//    (Broadcast 64 KiB 4.62 against 3.90, 128 KiB 4.89 against 5.08, 4 MiB
-//    12.4 against 39.6; Reduce 4.78 against 5.24 and 18.0 against 38.4).  At
-//    4-7 ranks Broadcast 1 MiB (4 ranks: 512 KiB 4.74 against 4.53, 1 MiB
-//    5.29 against 6.10), Reduce 2 MiB (5 ranks: 1 MiB 6.57 against 5.62,
-//    4 MiB 13.0 against 14.8).  At 2-3 ranks Broadcast 4 MiB (2 ranks: 1 MiB
-//    4.36 against 4.05, 4 MiB 6.54 against 7.01), Reduce 16 MiB.
+// Bytes (AllReduce, ReduceScatter: all ranks' inputs; AllGather: one rank's
+// output; Broadcast, Reduce: the message) from which a call runs on a ring kernel
+// (ll_ring.hpp), measured on MI355X at every rank count against the kernel that
+// serves smaller calls, bfloat16, back-to-back calls, at sizes 2-20 % apart.
+// Below, "a / b" is that kernel's time and the ring's, in us, at a size per rank;
+// "odd" are streams with an odd number of elements, whose rows lie on half words
+// and cost both of them more.
+//  - AllReduce, lines: 7 MiB (2 ranks: 3 MiB 6.44 / 7.08, 3.7 MiB 7.59 / 7.33; 4
+//    ranks: 1 MiB 6.34 / 7.27, 1.9 MiB 9.41 / 8.25; 8 ranks odd: 934 KiB 12.5 /
+//    11.8), at 8 ranks 7.5 MiB (932 KiB 9.61 / 9.91, 970 KiB 10.5 / 9.98).
+//    8-byte packets: 5 MiB (8 ranks: 512 KiB 8.48 / 8.77, 717 KiB 11.7 / 10.8; 4
+//    ranks: 1.34 MiB 10.9 / 9.42), at 8 ranks odd 6.5 MiB (742 KiB 12.3 / 12.9, 861
+//    KiB 14.6 / 14.4).
+//  - ReduceScatter: 32 MiB (8 ranks: 2 MiB 9.7 / 12.6, 4.2 MiB 25.3 / 17.9; 4 ranks:
+//    4 MiB 9.3 / 10.3, 8.4 MiB 21.5 / 18.1).  8-byte packets at 6 ranks 38 MiB (6.2
+//    MiB 31.6 / 32.2, 6.4 MiB 32.2 / 31.1); at 2 ranks never (20.9 MiB 26.0 / 28.4, 74
+//    MiB 80.1 / 85.3) but for odd streams (27.0 MiB 39.1 / 35.9).
+//  - AllGather: 256 KiB, up to which the one-tile kernel serves (4 ranks: 32 KiB
+//    2.82 / 2.98, 64 KiB 3.19 / 2.99; 8 ranks: 28 KiB 3.25 / 3.22, 32 KiB 3.84 / 3.11).
+//    8-byte packets, odd: at 2 ranks 1.6 MiB (650 KiB 4.22 / 4.57, 822 KiB 4.70 /
+//    4.66), at 3 and 4 ranks 512 KiB (4 ranks: 102 KiB 3.86 / 4.15, 130 KiB 4.58 /
+//    4.25).
+//  - Broadcast: at 8 ranks, a rank per XCD, 128 KiB (64 KiB 3.90 / 4.62, 147 KiB
+//    5.60 / 5.37), odd 256 KiB with lines (230 KiB 6.40 / 7.10, 268 KiB 7.43 / 7.08)
+//    and 192 KiB with 8-byte packets (171 KiB 6.43 / 6.76, 198 KiB 7.10 / 6.80); at 4-7
+//    ranks 1 MiB (4 ranks: 512 KiB 4.53 / 4.74, 1.1 MiB 6.34 / 5.92); at 2 and 3 ranks 4
+//    MiB (2 ranks: 1 MiB 4.05 / 4.36, 4.2 MiB 7.18 / 6.84).
+//  - Reduce: at 8 ranks as Broadcast (147 KiB 5.55 / 5.22; odd, lines: 198 KiB 6.38 /
+//    6.62, 268 KiB 7.35 / 7.00); at 7 ranks 2 MiB (12.2 / 12.1), odd with lines 2.25
+//    MiB (2 MiB 13.0 / 13.9, 2.3 MiB 14.2 / 14.3); at 6 ranks 2 MiB, with lines 2096 KiB
+//    (2076 KiB 9.67 / 11.5, 2104 KiB 11.7 / 11.2); at 5 ranks 2.5 MiB with 8-byte packets
+//    (2.3 MiB 14.6 / 15.1, 2.5 MiB 15.9 / 14.2), 3 MiB with lines (2.9 MiB 11.8 / 12.3,
+//    3.1 MiB 12.4 / 12.0); at 4 ranks 2 MiB (9.40 / 8.18); at 2 and 3 ranks 16 MiB (2
+//    ranks: 17.1 MiB 17.4 / 17.0), but with 8-byte packets at 3 ranks never (16.4 MiB
+//    34.9 / 38.3, 67 MiB 132 / 139).
 // A bounded-scratch call of several iterations always does: it would pay two
-// exchanges per iteration (32 MiB at 8 ranks in 1 MiB iterations 345 -> 161
-// us, in 256 KiB iterations 540 -> 219 us).
-bool ring_size_ok(int mode, const Plan &pl, uint64_t total) {
-  const uint64_t KiB = 1024, MiB = 1024 * 1024;
-  const int P = pl.P;
+// exchanges per iteration (32 MiB at 8 ranks: iterations of 1 MiB 339 / 163, of 256
+// KiB 540 / 219; messages of 1.2 to 40 iterations of 1 KiB to 1 MiB at 2-8 ranks:
+// never slower).
+uint64_t ring_from_bytes(int mode, int P, bool line, bool odd) {
+  constexpr uint64_t KiB = 1024, MiB = 1024 * 1024, never = ~0ull;
   switch (mode) {
-    case RING_AR: return pl.a.iters > 1 || total * P >= (pl.proto == PR_LINE ? 7 : 5) * MiB;
-    case RING_RS: return total * P >= 32 * MiB;
-    case RING_AG: return total >= 256 * KiB;
-    case RING_BCAST: return total >= (P == 8 ? 128 * KiB : (P >= 4 ? 1 * MiB : 4 * MiB));
-    default: return total >= (P == 8 ? 128 * KiB : (P >= 4 ? 2 * MiB : 16 * MiB));
+    case RING_AR:
+      if (line) return P == 8 && !odd ? 7680 * KiB : 7 * MiB;
+      return P == 8 && odd ? 6656 * KiB : 5 * MiB;
+    case RING_RS:
+      if (!line && P == 2 && !odd) return never;
+      return (!line && P == 6 ? 38 : 32) * MiB;
+    case RING_AG:
+      if (!line && odd && P <= 4) return (P == 2 ? 1600 : 512) * KiB;
+      return 256 * KiB;
+    case RING_BCAST:
+      if (P == 8) return (odd ? (line ? 256 : 192) : 128) * KiB;
+      return (P >= 4 ? 1 : 4) * MiB;
+    default:
+      switch (P) {
+        case 8: return (odd ? (line ? 256 : 192) : 128) * KiB;
+        case 7: return (line && odd ? 2304 : 2048) * KiB;
+        case 6: return (line ? 2096 : 2048) * KiB;
+        case 5: return (line ? 3072 : 2560) * KiB;
+        case 4: return 2 * MiB;
+        case 3: return line ? 16 * MiB : never;
+        default: return 16 * MiB;
+      }
   }
+}
+
+bool ring_size_ok(int mode, const Plan &pl, uint64_t total, bool odd) {
+  if (mode == RING_AR && pl.a.iters > 1) return true;
+  const uint64_t bytes = mode == RING_AR || mode == RING_RS ? total * (uint64_t)pl.P : total;
+  return bytes >= ring_from_bytes(mode, pl.P, pl.proto == PR_LINE, odd);
 }
 
 // Waves per CU of a ring launch.  The kernels are bound by the fabric (about
@@ -478,9 +512,9 @@ int ring_plan(const Plan &pl, RingPlan *rp, bool *serves) {
   const bool blocks = mode == RING_RS || mode == RING_AG;  // P chunks of n elements
   rp->mode = mode;
   rp->total = (uint64_t)pl.a.n * (uint64_t)es * (blocks ? (uint64_t)P : 1);
-  if (rp->total > L::kRingMaxBytes || !ring_size_ok(mode, pl, rp->total)) return LL_OK;
-  rp->chunk = blocks ? rp->total / (uint64_t)P : L::twoshot_chunk((uint64_t)pl.a.n, P, es) * (uint64_t)es;
   const int odd = pl.a.al4 == 0 || (pl.a.in != nullptr && pl.a.in_al4 == 0) ? 1 : 0;  // bfloat16 only
+  if (rp->total > L::kRingMaxBytes || !ring_size_ok(mode, pl, rp->total, odd != 0)) return LL_OK;
+  rp->chunk = blocks ? rp->total / (uint64_t)P : L::twoshot_chunk((uint64_t)pl.a.n, P, es) * (uint64_t)es;
   rp->fn = table().ring[mode][pl.proto == PR_LINE ? 1 : 0][pl.dt + odd][P];
   int cap = 0;
   int st = resident_grid(reinterpret_cast<const void *>(rp->fn), kRingThreads, &cap);

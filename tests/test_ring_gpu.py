@@ -108,12 +108,31 @@ def scratch_area(d, packet8):
     return (0, 2 * a8) if packet8 else (2 * a8, 2 * a8 + 2 * a128)
 
 
-# (operation, first size per rank in bytes on the ring, by rank count)
+# First size in bytes on the ring, by rank count, whether the stream has an odd
+# number of bfloat16 elements, and packet format (per rank; AllGather: sent).
+NEVER = 1 << 40
+
+
+def first_rooted(p, odd, line):
+    if p == 8:
+        return (256 if line else 192) * KIB if odd else 128 * KIB
+    return None
+
+
+def first_reduce(p, odd, line):
+    by = {7: 2304 if line and odd else 2048, 6: 2096 if line else 2048, 5: 3072 if line else 2560, 4: 2048, 2: 16384,
+          3: 16384 if line else NEVER}
+    return first_rooted(p, odd, line) or by[p] * KIB
+
+
 FIRST = {
-    "allreduce": lambda p: -(-7 * MIB // p), "reduce_scatter": lambda p: -(-32 * MIB // p),
-    "allgather": lambda p: -(-256 * KIB // p),
-    "broadcast": lambda p: 128 * KIB if p == 8 else (MIB if p >= 4 else 4 * MIB),
-    "reduce": lambda p: 128 * KIB if p == 8 else (2 * MIB if p >= 4 else 16 * MIB),
+    "allreduce": lambda p, odd=False, line=True: -(-((7680 if p == 8 and not odd else 7168) if line else
+                                                     (6656 if p == 8 and odd else 5120)) * KIB // p),
+    "reduce_scatter": lambda p, odd=False, line=True: NEVER if p == 2 and not line and not odd else
+    -(-(38 if p == 6 and not line else 32) * MIB // p),
+    "allgather": lambda p, odd=False, line=True: -(-(256 if line or not odd or p > 4 else 1600 if p == 2 else 512) * KIB // p),
+    "broadcast": lambda p, odd=False, line=True: first_rooted(p, odd, line) or (MIB if p >= 4 else 4 * MIB),
+    "reduce": lambda p, odd=False, line=True: first_reduce(p, odd, line),
 }
 
 
@@ -167,7 +186,7 @@ def test_streams_that_start_and_end_on_half_a_word(op, p):
     stream's last element is half of one.  The half word at every place of a
     lane, at a tile's and a chunk's first and last word, and in 8-byte packets."""
     unit = p if op == "reduce_scatter" else 1
-    base = -(-FIRST[op](p) // 2 // unit) | 1  # elements of a chunk (ReduceScatter) or of the message
+    base = -(-FIRST[op](p, odd=True) // 2 // unit) | 1  # elements of a chunk (ReduceScatter) or of the message
     tile = 480 * (1 if op in ("allgather", "reduce_scatter") else p)
     top = base // tile * tile + 3 * tile
     counts = [base, base + 2, base + 4, base + 6, top - 1, top + 1]
@@ -177,7 +196,29 @@ def test_streams_that_start_and_end_on_half_a_word(op, p):
         check(reg, op, m * unit, p, "bf16", p - 1, True, f"{op} P={p} odd count {m}")
     kw = {"algo": "twoshot_waves"} if op == "allreduce" else {"proto": "packet8"}
     for m in (counts[0], counts[1]):
-        check(reg, op, m * unit, p, "bf16", 0, True, f"{op} P={p} odd count {m} packet8", **kw)
+        ring = 2 * m * unit >= FIRST[op](p, odd=True, line=False)
+        check(reg, op, m * unit, p, "bf16", 0, ring, f"{op} P={p} odd count {m} packet8", **kw)
+
+
+@pytest.mark.parametrize("op,p,odd,line", [
+    ("allreduce", 8, True, False), ("reduce_scatter", 6, False, False), ("reduce_scatter", 2, False, False),
+    ("allgather", 2, True, False), ("allgather", 4, True, False), ("broadcast", 8, True, True),
+    ("broadcast", 8, True, False), ("reduce", 8, True, True), ("reduce", 7, True, True), ("reduce", 6, False, True),
+    ("reduce", 5, False, False), ("reduce", 3, False, False)])
+def test_first_sizes_that_differ_by_format_and_odd_streams(op, p, odd, line):
+    """Just below and at the first size on the ring; a large message where the
+    ring never serves."""
+    unit = p if op == "reduce_scatter" else 1
+    first = FIRST[op](p, odd, line)
+    never = first >= NEVER
+    m = -(-(20 * MIB if never else first) // (2 * unit))
+    m += (m + odd) % 2
+    reg = SymRegion(p, m * unit, "bf16", out_elems=out_elems(op, p, m * unit) + 4096)
+    reg.init()
+    kw = {"algo": "twoshot_line_waves" if line else "twoshot_waves"} if op == "allreduce" else {
+        "proto": "line128" if line else "packet8"}
+    for k, ring in ((m - 2, False), (m, not never)):
+        check(reg, op, k * unit, p, "bf16", p - 1, ring, f"{op} P={p} odd={odd} {kw} {k * unit} elements", **kw)
 
 
 def test_ring_and_other_kernels_share_a_region():
