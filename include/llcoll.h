@@ -292,8 +292,10 @@ int ll_allgather_ex(void *sym_base, size_t rank_stride, void *out, size_t sendco
  * sub-buffer (each receive is the credit for the next send).  In sentinel
  * mode every lane also waits for its slot resets to be acknowledged before
  * the next iteration.  The flagged two-shot algorithms run a call of up to
- * 2 GiB per rank in one pass instead, with the sub-buffers as a ring of packet
- * positions and the same credit; such a call still uses k epochs.
+ * 2 GiB - 1 MiB per rank in one pass instead, with the sub-buffers as a ring of
+ * packet positions and the same credit, unless a tuning field is set that the ring
+ * kernels do not have (lltune.h) or the sub-buffers hold less than one workgroup's
+ * ring (about 2 KiB iterations at 8 ranks); such a call still uses k epochs.
  *
  * Epochs: such a call uses the k epochs epoch .. epoch+k-1 (*epochs_used =
  * k, 0 when count is 0); the next call on the same scratch region must use an

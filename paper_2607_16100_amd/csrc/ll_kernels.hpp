@@ -106,10 +106,12 @@ __device__ __forceinline__ KArgs pin_args(const KArgs &k) {
 // k_twoshot_tile, k_rooted_tile), which run at the sizes where a call's latency
 // is a chain of a few round trips, and fetching the arguments is the first of
 // them.  What a wave needs before its last store lies in the first 64 bytes: one
-// scalar load of one cache line.  The rest is loaded where it is used, which is
-// off that chain.  With all of KArgs fetched up front, 224 bytes, a 16 KiB
-// AllReduce at 8 ranks took 3.31 us, with these 3.23; 2 KiB 2.85 and 2.70; 64 KiB
-// (two-shot) 4.28 and 4.25.
+// scalar load of one cache line.  Of the rest only `stamps` is read before that,
+// by the test at a kernel's start; it is fetched along with the first line, and a
+// bit for it there instead gained nothing (16 KiB: 3.23 against 3.25 us).  The
+// others are loaded where they are used, off that chain.  With all of KArgs
+// fetched up front, 224 bytes, a 16 KiB AllReduce at 8 ranks took 3.31 us, with
+// these 3.23; 2 KiB 2.85 and 2.70; 64 KiB (two-shot) 4.28 and 4.25.
 struct TileArgs {
   const char *in;       // as in KArgs
   uint64_t in_stride;

@@ -14,18 +14,21 @@
 //    ranks moves 3.3 GB with it and 2.1 GB without.
 //  - A ring of packets.  A wave reuses kRingEntries positions of 1 KiB per
 //    peer instead of a slot position per tile, so the packets of a call of any
-//    size live in at most 56 MiB at 8 ranks, which that cache can hold.  Each peer's
-//    packets are the credit to go on (see kRingEntries), so a ring needs no
+//    size live in at most 56 MiB at 8 ranks, which that cache can hold (a
+//    Broadcast's packets have a position per tile and grow with the message).  Each
+//    peer's packets are the credit to go on (see kRingEntries), so a ring needs no
 //    counter, no barrier and no second buffer; a bounded-scratch call needs no
 //    iterations.
 //  - Waves that work alone.  A wave takes a tile of every chunk: it sends P-1
 //    tiles and reduces one, all in registers, with no LDS and no workgroup
 //    barrier, and its next tile's packets go out before it waits.
-// Measured (8 ranks, bfloat16 unless said, against the kernels that pass the
-// result through scratch): AllReduce 1 MiB 10.7 -> 9.2 us, 4 MiB 31.1 -> 22,
-// 16 MiB 124 -> 79, 64 MiB of binary32 500 -> 308; AllGather 448 KiB sent
-// 17.7 -> 8.1; Broadcast 16 MiB 146 -> 42; Reduce 16 MiB 146 -> 65; bounded
-// scratch, 32 MiB in 1 MiB iterations 345 -> 161.
+// Measured (8 ranks, bfloat16 unless said, back-to-back calls on one region,
+// against the kernels that pass the result through scratch): AllReduce 1 MiB 10.7
+// -> 9.6 us, 4 MiB 31.4 -> 21.9, 16 MiB 124 -> 78 (86 from a program's calls on
+// changing inputs), 64 MiB of binary32 504 -> 317; AllGather 448 KiB sent 17.5 ->
+// 8.0; Broadcast 16 MiB 146 -> 42; Reduce 16 MiB 147 -> 62; bounded scratch, 32 MiB
+// in 1 MiB iterations 339 -> 163.  The figures beside single choices below compare
+// two forms in the same run.
 //
 // Grid = P * W workgroups of kRingThreads threads; workgroup b serves rank
 // r = b % P, and its waves are numbered g = (b / P) * waves + wave, G of them

@@ -256,6 +256,10 @@ struct Plan {
   uint64_t area_bytes = 0;   // bytes of the call's packet area from a.area on
 };
 
+// The rules from here to clear_slots serve the calls that no ring kernel takes
+// (ring_plan): below its sizes every call; at and above them sentinel units, calls
+// with a tuning field set, and streams above kRingMaxBytes.
+//
 // Launch shape of the two-shot AllReduce with one wave per peer, measured on
 // MI355X (bfloat16, P = 2, 4, 6, 8, 128 KiB - 8 MiB per rank, p50 of
 // back-to-back calls).  A workgroup has P waves, so a grid of G workgroups
@@ -314,7 +318,8 @@ bool twoshot_tile_ok(const Plan &pl, int wpr, int lu, tile_fn *tf, int64_t *tile
 //  - lines (a line unit is a whole wave): two units per lane once the P
 //    tiles of a step hold more than 1200 line units, four once they hold
 //    more than 8192 (from about 8 MiB per rank, where the kernel is bound by
-//    bandwidth and fewer, longer waves move the bytes faster);
+//    bandwidth and fewer, longer waves move the bytes faster; tuned calls
+//    only, the ring has the others);
 //  - 8-byte packets and sentinel units: two once a chunk has more tiles of
 //    64 units than resident workgroups per rank.
 // Elsewhere two units per lane are never more than about 3 % faster and up
@@ -333,7 +338,9 @@ int wave_units_log2(const Plan &pl, int wpr) {
     // four from 512 KiB if its workgroups then hold at most 16 waves per CU
     // (8 ranks, b = 128: 11.41 -> 10.09 us; 4 ranks, b = 256: 9.85 -> 9.28
     // us), otherwise two (8 ranks, b = 256: 23.3 us in the one-lane kernel,
-    // 17.9 us).
+    // 17.9 us).  From the ring's first size on (ring_from_bytes) a flagged
+    // AllGather is the ring's (b = 256: 8.0 us), so its two rules serve sentinel
+    // units, tuned calls and a few odd streams.
     const uint64_t data = (uint64_t)pl.a.n * (pl.dt == LL_BF16 ? 2u : 4u) * (uint64_t)pl.P;
     const uint64_t KiB = 1024;
     if (data < 256 * KiB) return 0;
@@ -472,9 +479,9 @@ bool ring_size_ok(int mode, const Plan &pl, uint64_t total, bool odd) {
 
 // Waves per CU of a ring launch.  The kernels are bound by the fabric (about
 // 6.6 TB/s of reads and writes together), not by latency, from 4 waves per CU
-// on: 64 MiB at 8 ranks 312 us with 4, 308 with 8, 311 with 16; 16 MiB 84, 79
-// and 79-100.  Fewer waves also keep the ring small: 8 per CU are 56 MiB of
-// slots at 8 ranks, which stay in the memory-side cache.  At 2 and 3 ranks a
+// on (compared in one run: 64 MiB at 8 ranks 312 us with 4, 308 with 8, 311 with
+// 16; 16 MiB 84, 79 and 79-100).  Fewer waves also keep the ring small: 8 per CU are
+// 56 MiB of slots at 8 ranks, which stay in the memory-side cache.  At 2 and 3 ranks a
 // wave has only one or two peers' tiles in flight, and 16 are faster (2 ranks,
 // 16 MiB: ReduceScatter 17.1 -> 14.6 us, Broadcast 15.1 -> 12.3, Reduce 17.3 ->
 // 15.1, AllReduce 18.1 -> 17.5; 3 ranks: Broadcast 21.9 -> 19.3, AllReduce 8 MiB
@@ -782,12 +789,17 @@ KArgs base_args(void *sym_base, size_t rank_stride, void *out, uint32_t epoch) {
 // crosses over at the same byte sizes); M = input bytes per rank.  Flags only
 // unless the caller allows sentinel mode, which wins from the smallest sizes
 // up to 1-8 MiB (by rank count), as the paper observes for larger messages
-// and rank counts.
+// and rank counts.  The upper limits of the sentinel two-shot (two_max) were
+// measured against the line two-shot before the ring kernels served it: near
+// them the ring is the faster one at some rank counts (2 ranks, 8 MiB: sentinel
+// units 13.3 us, the ring 10.4; 5 ranks, 2 MiB: 12.7 and 11.2; 8 ranks, 1 MiB:
+// 9.6 and 9.9).
 ll_algo auto_algo(uint64_t in_bytes, int P, bool sentinel_ok) {
   const uint64_t KiB = 1024, MiB = 1024 * 1024;
-  // the line two-shot with one wave per peer at every size up to the
-  // maximum, except above 16 MiB at 5-6 ranks, where the one-lane line
-  // two-shot is faster (measured at 8-64 MiB, binary32)
+  // the line two-shot: the ring kernel serves either name at the sizes where
+  // it is the faster one.  Where it does not (tuned calls, streams above
+  // kRingMaxBytes), the kernel with one wave per peer, except above 16 MiB at
+  // 5-6 ranks, where the one-lane kernel is faster (8-64 MiB, binary32)
   const uint64_t line_waves_max = (P == 5 || P == 6) ? 16 * MiB : L::kMaxInputBytes;
   auto large = [&]() { return in_bytes <= line_waves_max ? LL_ALGO_TWOSHOT_LINE_WAVES : LL_ALGO_TWOSHOT_LINE; };
   // With sentinel mode allowed, messages of at most 8 KiB at 3 or more ranks
@@ -844,8 +856,11 @@ ll_algo auto_algo(uint64_t in_bytes, int P, bool sentinel_ok) {
 // 8 MiB at 4 and 8 ranks: ReduceScatter with 8-byte packets up to 128 KiB
 // and lines above (4 ranks, b = 16, 224 KiB: 3.20 us with 8-byte packets,
 // 3.08 us with lines); AllGather with lines at every size (8 ranks, b = 1,
-// 14 KiB: 3.28 us with 8-byte packets, 3.08 us with lines); with sentinel
-// mode allowed, sentinel units up to 2 MiB (4 MiB at 2-4 ranks).
+// 14 KiB: 3.28 us with 8-byte packets, 3.08 us with lines; on the ring, where
+// the format is that of the completion flags and of the lane's share of a tile,
+// the two lie within 5 %: b = 256 8.3 us with lines, 8.0 with 8-byte packets);
+// with sentinel mode allowed, sentinel units up to 2 MiB (4 MiB at 2-4 ranks),
+// but not for an AllGather that a ring kernel serves (ll_allgather_ex).
 ll_proto auto_proto(uint64_t bytes, int P, bool sentinel_ok, bool allgather) {
   const uint64_t KiB = 1024, MiB = 1024 * 1024;
   if (sentinel_ok) return bytes <= (P >= 5 ? 2 : 4) * MiB ? LL_PROTO_SENTINEL : LL_PROTO_LINE128;
@@ -867,7 +882,10 @@ ll_proto auto_proto_rooted(uint64_t bytes, bool sentinel_ok) {
 // (measured at 4 and 8 ranks): 8-byte packets and sentinel units up to
 // 2 MiB of data per rank; lines up to 8 MiB at 2-4 ranks and 4 MiB at 5-8
 // ranks (8 ranks, b = 256, 3.5 MiB: AllGather 23.3 us with one lane per
-// unit, 17.9 us with one wave per peer at two units per lane).
+// unit, 17.9 us with one wave per peer at two units per lane).  The ring takes
+// the flagged AllGather from 256 KiB and the ReduceScatter from 32 MiB over the
+// ranks on (ring_from_bytes), whichever family is named here, so for the AllGather
+// these limits decide for sentinel units and tuned calls.
 // ll_tuning.wave_kernels forces either family.
 bool use_wave_kernel(ll_proto proto, uint64_t bytes, int P, bool allgather, const CallOpts &o) {
   (void)allgather;
