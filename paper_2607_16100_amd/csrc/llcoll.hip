@@ -856,9 +856,10 @@ ll_algo auto_algo(uint64_t in_bytes, int P, bool sentinel_ok) {
 // 8 MiB at 4 and 8 ranks: ReduceScatter with 8-byte packets up to 128 KiB
 // and lines above (4 ranks, b = 16, 224 KiB: 3.20 us with 8-byte packets,
 // 3.08 us with lines); AllGather with lines at every size (8 ranks, b = 1,
-// 14 KiB: 3.28 us with 8-byte packets, 3.08 us with lines; on the ring, where
-// the format is that of the completion flags and of the lane's share of a tile,
-// the two lie within 5 %: b = 256 8.3 us with lines, 8.0 with 8-byte packets);
+// 14 KiB: 3.28 us with 8-byte packets, 3.08 us with lines; chosen before the
+// ring kernel, where the format is only the shape of a tile and 8-byte packets
+// are the faster one: 8 ranks, 32 KiB sent 3.50 us against 3.64, 256 KiB 5.95
+// against 6.78, b = 256 8.0 against 8.3);
 // with sentinel mode allowed, sentinel units up to 2 MiB (4 MiB at 2-4 ranks),
 // but not for an AllGather that a ring kernel serves (ll_allgather_ex).
 ll_proto auto_proto(uint64_t bytes, int P, bool sentinel_ok, bool allgather) {
@@ -1564,7 +1565,7 @@ int ll_allgather_ex(void *sym_base, size_t rank_stride, void *out, size_t sendco
     const unsigned flagged = allowed & (L::kFmt8 | L::kFmtLine);
     if (proto == LL_PROTO_SENTINEL && flagged != 0 && sendcount != 0) {
       // sentinel units are slower than a ring kernel, whose packets carry no
-      // data (8 ranks, 128 KiB per rank sent: 6.4 us against 4.7), and have none
+      // data (8 ranks, 128 KiB per rank sent: 6.4 us against 5.1 with lines)
       const ll_proto named = proto_choice(LL_PROTO_LINE128, flagged);
       const Plan pl = plan_with(named);
       RingPlan rp;
